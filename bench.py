@@ -97,7 +97,7 @@ def kernel_peak(name):
 def source_hash():
     h = hashlib.sha256()
     for f in ("ifq_conv.hip", "ifq_conv_mfma.hip", "ifq_conv_halo.hip", "ifq_conv_small.hip",
-              "ifq_conv_w2.hip", "ifq_conv_wp.hip", "ifq_epilogue.h", "ifq_mfma_common.h",
+              "ifq_conv_w2.hip", "ifq_conv_wp.hip", "ifq_conv_win.hip", "ifq_epilogue.h", "ifq_mfma_common.h",
               "ifq_pool.hip"):
         with open(os.path.join(ROOT, "paper_1911_08076_amd", "csrc", f), "rb") as fh:
             h.update(fh.read())

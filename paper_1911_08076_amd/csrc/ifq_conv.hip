@@ -1,7 +1,8 @@
 // Generic integrated fixed-point quantized convolution on gfx950 (MI355X):
-// every layer shape and code layout the fast path (ifq_conv_mfma.hip) does
-// not take: byte-per-code input, 8-bit input codes, c_in not a multiple of
-// 64, 2-bit NHWC input with 16 | c_in.
+// every layer shape and code layout that the fast path (ifq_conv_mfma.hip)
+// and the windowed kernel (ifq_conv_win.hip) do not take: 8-bit input codes,
+// c_in not a multiple of 16, inputs not aligned to the windowed kernel's
+// cells, windows that do not fit its LDS. Also the dispatcher over all kernels.
 //
 // One kernel computes a quantized substructure of IFQ-Net:
 //   a    = W_b (x) X_q            integer part of Eq. (1), as an implicit GEMM
@@ -331,6 +332,7 @@ const char* conv_kernel_name(const ConvLaunch& a) {
   if (mfma_eligible(a)) return conv_mfma_name(a);
   if (small8_eligible(a)) return conv_small8_name(a);
   if (small2_eligible(a)) return conv_small2_name(a);
+  if (win_eligible(a)) return conv_win_name(a);
   static const char* names[3][4] = {
       {"conv_igemm<16, 256, 1, 0>", "conv_igemm<32, 128, 1, 0>",
        "conv_igemm<64, 128, 2, 0>", "conv_igemm<128, 128, 2, 0>"},
@@ -359,6 +361,7 @@ hipError_t launch_conv(const ConvLaunch& a, hipStream_t stream) {
   if (mfma_eligible(a)) return launch_conv_mfma(a, stream);
   if (small8_eligible(a)) return launch_conv_small8(a, stream);
   if (small2_eligible(a)) return launch_conv_small2(a, stream);
+  if (win_eligible(a)) return launch_conv_win(a, stream);
   switch (gather_kind(a)) {
     case kGatherU2: return launch_gather<kGatherU2>(a, stream);
     case kGatherI8: return launch_gather<kGatherI8>(a, stream);

@@ -305,6 +305,12 @@ inline bool fused_supported(const ConvLaunch& a) {
   return plan_halo(a, &p) || plan_w2(a, -1, &w);
 }
 
+// Any filter size and stride on byte codes (below 8 bits) or 2-bit NHWC codes,
+// c_in a multiple of 16, input windows resident in LDS.
+bool win_eligible(const ConvLaunch& a);
+hipError_t launch_conv_win(const ConvLaunch& a, hipStream_t stream);
+const char* conv_win_name(const ConvLaunch& a);
+
 // 8-bit input codes with c_in <= 4 (a detector's first layer): whether the
 // small-channel kernel takes the layer, its launch and its name.
 bool small8_eligible(const ConvLaunch& a);

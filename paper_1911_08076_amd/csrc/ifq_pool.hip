@@ -1,10 +1,13 @@
 // Integer max-pool on codes (Eq. 4 applied to the quantizer output) and
 // conversion between the code layouts.
 //
-// Both are HBM-bound streaming kernels: each thread owns a vector of V bytes
-// of one output pixel (V = 16, 4 or 1, the widest that divides the bytes per
-// pixel), reads the k x k window of input vectors (in-bounds positions only)
-// and keeps a per-code running maximum with SWAR byte arithmetic.
+// Both stream HBM, and on the networks' tensors (0.1 to 16 MB) latency decides:
+// a thread owns a vector of V bytes of one output pixel (V = 16, 4 or 1, the
+// widest that divides the bytes per pixel) and has every load of its window
+// in flight before the first compare; indexes are 32-bit with divisions by
+// multiplication. Before, each position's loads waited for the last compare
+// behind 64-bit divisions: 3x3/2 on 64x55x55x96 2-bit codes 6.7 -> 3.5 us,
+// on 32x13x13x256 5.7 -> 3.2 us, where a launch alone is 3.0 us.
 #include <hip/hip_runtime.h>
 
 #include "ifq_internal.h"
@@ -12,107 +15,133 @@
 namespace ifq {
 namespace {
 
-// Per-byte unsigned max of four bytes, valid for byte values below 128:
-// (b | 0x80) - a never borrows across bytes and its top bit says b >= a.
-__device__ __forceinline__ uint32_t max7(uint32_t a, uint32_t b) {
-  const uint32_t d = (b | 0x80808080u) - a;
-  const uint32_t m = ((d >> 7) & 0x01010101u) * 0xFFu;
-  return (b & m) | (a & ~m);
+typedef unsigned short u16x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t fdivu(uint32_t n, FastDiv d) {
+  return (__umulhi(n, d.mul) + n) >> d.shift;
 }
 
-// Per-byte unsigned max for any byte values.
-__device__ __forceinline__ uint32_t max8(uint32_t a, uint32_t b) {
-  uint32_t r = 0;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const uint32_t x = (a >> (8 * i)) & 0xFFu;
-    const uint32_t y = (b >> (8 * i)) & 0xFFu;
-    r |= (x > y ? x : y) << (8 * i);
+struct PoolGeom {
+  FastDiv div_nv, div_wo, div_ho;   // vectors per pixel, output columns, rows
+  int32_t total;                    // vectors in all
+  int32_t cb;                       // bytes per pixel
+};
+
+// Running maximum over words of codes. Bytes: even and odd bytes as 16-bit
+// halves. 2-bit fields: h collects the high bits, and in a second pass l the
+// low bits of the fields whose high bit equals the maximum's.
+template <bool U2>
+__device__ __forceinline__ uint32_t window_max(const uint32_t* v, int n, int stride) {
+  if constexpr (U2) {
+    uint32_t hi = 0, lo = 0;
+    for (int i = 0; i < n; ++i) hi |= v[i * stride];
+    hi &= 0xAAAAAAAAu;
+    for (int i = 0; i < n; ++i) {
+      const uint32_t t = v[i * stride];
+      lo |= t & ~((hi ^ t) >> 1);
+    }
+    return hi | (lo & 0x55555555u);
+  } else {
+    u16x2 e = {0, 0}, o = {0, 0};
+    for (int i = 0; i < n; ++i) {
+      const uint32_t t = v[i * stride];
+      e = __builtin_elementwise_max(e, __builtin_bit_cast(u16x2, t & 0x00FF00FFu));
+      o = __builtin_elementwise_max(o, __builtin_bit_cast(u16x2, t & 0xFF00FF00u));
+    }
+    return __builtin_bit_cast(uint32_t, e) | __builtin_bit_cast(uint32_t, o);
   }
-  return r;
 }
 
-// Per-field max of sixteen 2-bit codes packed four per byte.
-__device__ __forceinline__ uint32_t max2(uint32_t a, uint32_t b) {
-  uint32_t r = 0;
-#pragma unroll
-  for (int f = 0; f < 4; ++f) {
-    const uint32_t x = (a >> (2 * f)) & 0x03030303u;
-    const uint32_t y = (b >> (2 * f)) & 0x03030303u;
-    r |= max7(x, y) << (2 * f);
+template <int V>
+__device__ __forceinline__ void load_vec(const uint8_t* p, uint32_t* v) {
+  if constexpr (V == 16) {
+    const uint4 q = *reinterpret_cast<const uint4*>(p);
+    v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+  } else if constexpr (V == 4) {
+    v[0] = *reinterpret_cast<const uint32_t*>(p);
+  } else {
+    v[0] = *p;
   }
-  return r;
 }
 
-// MODE 0: byte codes below 128; 1: any byte codes; 2: 2-bit packed codes.
-template <int MODE>
-__device__ __forceinline__ uint32_t vmax(uint32_t a, uint32_t b) {
-  if constexpr (MODE == 0) return max7(a, b);
-  else if constexpr (MODE == 1) return max8(a, b);
-  else return max2(a, b);
-}
-
-template <int V, int MODE>
-__global__ __launch_bounds__(256) void maxpool_codes(PoolLaunch a, int64_t total,
-                                                     int cb) {
-  const int nv = cb / V;
-  for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < total;
-       t += (int64_t)gridDim.x * blockDim.x) {
-    const int chunk = (int)(t % nv);
-    int64_t pix = t / nv;
-    const int px = (int)(pix % a.wo);
-    pix /= a.wo;
-    const int py = (int)(pix % a.ho);
-    const int b = (int)(pix / a.ho);
-    uint32_t m[(V + 3) / 4];
+// K: the window where fixed (every load of it in flight at once), 0: any, a
+// row of up to four positions at a time. Positions past the bottom or right
+// edge (SAME mode) read the edge, which the window holds already.
+template <int V, bool U2, int K>
+__global__ void maxpool_codes(PoolLaunch a, PoolGeom g) {
+  constexpr int W = V == 16 ? 4 : 1;
+  const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
+  if (t >= (uint32_t)g.total) return;
+  const uint32_t pix = fdivu(t, g.div_nv);
+  const uint32_t chunk = t - pix * (uint32_t)(g.cb / V);
+  const uint32_t row = fdivu(pix, g.div_wo);
+  const int px = (int)(pix - row * a.wo);
+  const uint32_t img = fdivu(row, g.div_ho);
+  const int py = (int)(row - img * a.ho);
+  const uint8_t* x = a.x + (int64_t)img * a.h * a.w * g.cb + chunk * V;
+  uint32_t m[W];
+  if constexpr (K > 0) {
+    uint32_t v[K * K * W];
 #pragma unroll
-    for (int q = 0; q < (V + 3) / 4; ++q) m[q] = 0u;
-    for (int i = 0; i < a.k; ++i) {
-      const int iy = py * a.stride + i;
-      if (iy >= a.h) break;
-      for (int jx = 0; jx < a.k; ++jx) {
-        const int ix = px * a.stride + jx;
-        if (ix >= a.w) break;
-        const uint8_t* src = a.x + ((int64_t)(b * a.h + iy) * a.w + ix) * cb + chunk * V;
-        if constexpr (V == 16) {
-          const uint4 v = *reinterpret_cast<const uint4*>(src);
-          m[0] = vmax<MODE>(m[0], v.x);
-          m[1] = vmax<MODE>(m[1], v.y);
-          m[2] = vmax<MODE>(m[2], v.z);
-          m[3] = vmax<MODE>(m[3], v.w);
-        } else if constexpr (V == 4) {
-          m[0] = vmax<MODE>(m[0], *reinterpret_cast<const uint32_t*>(src));
-        } else {
-          m[0] = vmax<MODE>(m[0], (uint32_t)*src);
-        }
+    for (int i = 0; i < K; ++i) {
+      const int iy = py * a.stride + i < a.h ? py * a.stride + i : a.h - 1;
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        const int ix = px * a.stride + j < a.w ? px * a.stride + j : a.w - 1;
+        load_vec<V>(x + (int64_t)(iy * a.w + ix) * g.cb, v + (i * K + j) * W);
       }
     }
-    uint8_t* dst = a.y + t * V;
-    if constexpr (V == 16) {
-      *reinterpret_cast<uint4*>(dst) = make_uint4(m[0], m[1], m[2], m[3]);
-    } else if constexpr (V == 4) {
-      *reinterpret_cast<uint32_t*>(dst) = m[0];
-    } else {
-      *dst = (uint8_t)m[0];
-    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) m[w] = window_max<U2>(v + w, K * K, W);
+  } else {
+#pragma unroll
+    for (int w = 0; w < W; ++w) m[w] = 0;
+    for (int i = 0; i < a.k && py * a.stride + i < a.h; ++i)
+      for (int j0 = 0; j0 < a.k && px * a.stride + j0 < a.w; j0 += 4) {
+        uint32_t v[5 * W];
+        const int jn = a.k - j0 < 4 ? a.k - j0 : 4;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int jx = px * a.stride + j0 + (j < jn ? j : 0);
+          load_vec<V>(x + (int64_t)((py * a.stride + i) * a.w + (jx < a.w ? jx : a.w - 1)) * g.cb,
+                      v + j * W);
+        }
+#pragma unroll
+        for (int w = 0; w < W; ++w) {
+          v[4 * W + w] = m[w];
+          m[w] = window_max<U2>(v + w, 5, W);
+        }
+      }
   }
+  uint8_t* dst = a.y + (int64_t)t * V;
+  if constexpr (V == 16) *reinterpret_cast<uint4*>(dst) = make_uint4(m[0], m[1], m[2], m[3]);
+  else if constexpr (V == 4) *reinterpret_cast<uint32_t*>(dst) = m[0];
+  else *dst = (uint8_t)m[0];
 }
 
-template <int MODE>
+template <bool U2>
 hipError_t launch_pool_mode(const PoolLaunch& a, int cb, hipStream_t stream) {
-  const int64_t pixels = (int64_t)a.n * a.ho * a.wo;
   auto go = [&](auto kern, int v) {
-    const int64_t total = pixels * (cb / v);
-    int64_t blocks = (total + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, stream, a,
-                       total, cb);
+    PoolGeom g;
+    g.cb = cb;
+    g.total = a.n * a.ho * a.wo * (cb / v);
+    g.div_nv = make_fastdiv(cb / v);
+    g.div_wo = make_fastdiv(a.wo);
+    g.div_ho = make_fastdiv(a.ho);
+    // small tensors: one wave a workgroup, spread over the CUs
+    const int nt = g.total <= 64 * 1024 ? 64 : 256;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((g.total + (int64_t)nt - 1) / nt)), dim3(nt), 0,
+                       stream, a, g);
     return hipGetLastError();
   };
-  if (cb % 16 == 0) return go(maxpool_codes<16, MODE>, 16);
-  if (cb % 4 == 0) return go(maxpool_codes<4, MODE>, 4);
-  return go(maxpool_codes<1, MODE>, 1);
+#define IFQ_POOL(V)                                         \
+  (a.k == 2 ? go(maxpool_codes<V, U2, 2>, V)                \
+            : a.k == 3 ? go(maxpool_codes<V, U2, 3>, V) : go(maxpool_codes<V, U2, 0>, V))
+  if (cb % 16 == 0) return IFQ_POOL(16);
+  if (cb % 4 == 0) return IFQ_POOL(4);
+  return IFQ_POOL(1);
+#undef IFQ_POOL
 }
 
 // Byte offset of the four codes of channel group cg (channels 4cg..4cg+3)
@@ -150,14 +179,85 @@ __global__ __launch_bounds__(256) void convert_codes(const uint8_t* src, uint8_t
   }
 }
 
+// Sixteen codes, one a byte (a 16-byte vector) <-> packed two bits each (a word).
+__device__ __forceinline__ uint32_t pack16(v4u v) {
+  auto byte = [](uint32_t w) {      // c0 | c1 << 2 | c2 << 4 | c3 << 6 of a word's low bits
+    w &= 0x03030303u;
+    w |= w >> 6;
+    return (w | w >> 12) & 0xFFu;
+  };
+  return byte(v.x) | byte(v.y) << 8 | byte(v.z) << 16 | byte(v.w) << 24;
+}
+__device__ __forceinline__ v4u unpack16(uint32_t u) {
+  auto word = [](uint32_t b) {
+    b = (b | b << 12) & 0x000F000Fu;
+    return (b | b << 6) & 0x03030303u;
+  };
+  return v4u{word(u & 0xFFu), word((u >> 8) & 0xFFu), word((u >> 16) & 0xFFu),
+                    word(u >> 24)};
+}
+
+// Conversions by units of 16 channels. convert_codes moves four at a time,
+// one byte of a 2-bit layout per thread: 9.1 us for 64x56x56x64 bytes to
+// BLOCK64 (16 MB, 1.8 TB/s), here 3.3 us (4.9 TB/s; the launch alone is 3.0);
+// 16x224x224x64 31 -> 10.5 us (6.1 TB/s). A thread has four units' loads in flight,
+// or one where four would leave CUs idle. Units run in
+// the order of the BLOCK64 side where there is one (unit 4*cell + j, so that
+// side is one contiguous stream and the other 64-byte spans), else in memory
+// order, where byte and packed NHWC tensors are both plain streams of units.
+// CELLS: 16-byte cells of 64 channels between the two 2-bit layouts instead.
+struct UnitGeom {
+  int32_t total;              // units (or cells)
+  int32_t hw, G;              // pixels per image, channel blocks of 64
+  FastDiv div_hw, div_g;
+};
+
+template <int SL, int DL, int U>
+__global__ __launch_bounds__(256) void convert_units(const uint8_t* src, uint8_t* dst,
+                                                     UnitGeom g) {
+  constexpr bool CELLS = SL != IFQ_LAYOUT_I8_NHWC && DL != IFQ_LAYOUT_I8_NHWC;
+  constexpr bool BLK = SL == IFQ_LAYOUT_U2_BLOCK64 || DL == IFQ_LAYOUT_U2_BLOCK64;
+  const uint32_t t0 = blockIdx.x * (256 * U) + threadIdx.x;
+  v4u v[U];
+  uint32_t so[U], po[U];
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    const uint32_t t = t0 + 256 * k < (uint32_t)g.total ? t0 + 256 * k : g.total - 1;
+    uint32_t nhwc = t;        // the unit's (cell's) place in the NHWC tensor
+    if constexpr (BLK) {
+      const uint32_t cell = CELLS ? t : t >> 2;
+      const uint32_t nb = fdivu(cell, g.div_hw), p = cell - nb * g.hw;
+      const uint32_t n = fdivu(nb, g.div_g), b = nb - n * g.G;
+      nhwc = (n * g.hw + p) * g.G + b;
+      if constexpr (!CELLS) nhwc = nhwc * 4 + (t & 3);
+    }
+    so[k] = SL == IFQ_LAYOUT_U2_BLOCK64 ? t : nhwc;
+    po[k] = DL == IFQ_LAYOUT_U2_BLOCK64 ? t : nhwc;
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    if constexpr (CELLS || SL == IFQ_LAYOUT_I8_NHWC)
+      v[k] = reinterpret_cast<const v4u*>(src)[so[k]];
+    else
+      v[k].x = reinterpret_cast<const uint32_t*>(src)[so[k]];
+  }
+#pragma unroll
+  for (int k = 0; k < U; ++k) {
+    if (t0 + 256 * k >= (uint32_t)g.total) continue;
+    if constexpr (CELLS) reinterpret_cast<v4u*>(dst)[po[k]] = v[k];
+    else if constexpr (SL == IFQ_LAYOUT_I8_NHWC)
+      reinterpret_cast<uint32_t*>(dst)[po[k]] = pack16(v[k]);
+    else reinterpret_cast<v4u*>(dst)[po[k]] = unpack16(v[k].x);
+  }
+}
+
 }  // namespace
 
 hipError_t launch_pool(const PoolLaunch& a, hipStream_t stream) {
   if ((int64_t)a.n * a.ho * a.wo == 0) return hipSuccess;
   if (a.layout == IFQ_LAYOUT_U2_NHWC_PACKED)
-    return launch_pool_mode<2>(a, a.c / 4, stream);
-  if (a.bits < 8) return launch_pool_mode<0>(a, a.c, stream);
-  return launch_pool_mode<1>(a, a.c, stream);
+    return launch_pool_mode<true>(a, a.c / 4, stream);
+  return launch_pool_mode<false>(a, a.c, stream);
 }
 
 hipError_t launch_convert(int64_t n, int64_t hw, int32_t c, int32_t src_layout,
@@ -165,6 +265,40 @@ hipError_t launch_convert(int64_t n, int64_t hw, int32_t c, int32_t src_layout,
                           hipStream_t stream) {
   const int64_t groups = n * hw * (c / 4);
   if (groups == 0) return hipSuccess;
+  // by units where the tensor is whole units on both sides, aligned for them
+  // (16 bytes, 4 for the packed side of a byte tensor), and indexes fit
+  const bool s8 = src_layout == IFQ_LAYOUT_I8_NHWC, d8 = dst_layout == IFQ_LAYOUT_I8_NHWC;
+  const bool blk = src_layout == IFQ_LAYOUT_U2_BLOCK64 || dst_layout == IFQ_LAYOUT_U2_BLOCK64;
+  const int64_t per = !s8 && !d8 ? 16 : 4;          // groups per unit or cell
+  const uintptr_t off = ((uintptr_t)src & (s8 || !d8 ? 15 : 3)) |
+                        ((uintptr_t)dst & (d8 || !s8 ? 15 : 3));
+  if (src_layout != dst_layout && groups % per == 0 && groups / per < ((int64_t)1 << 30) &&
+      off == 0) {
+    UnitGeom g;
+    g.total = (int32_t)(groups / per);
+    g.hw = blk ? (int32_t)hw : 1;
+    g.G = blk ? c / 64 : 1;
+    g.div_hw = make_fastdiv(g.hw);
+    g.div_g = make_fastdiv(g.G);
+    auto go = [&](auto k1, auto k4) {
+      // one unit a thread up to eight workgroups a CU
+      const int per_wg = g.total <= 8 * kPlanCUs * 256 ? 256 : 1024;
+      hipLaunchKernelGGL(per_wg == 256 ? k1 : k4, dim3((g.total + per_wg - 1) / per_wg), dim3(256),
+                         0, stream, reinterpret_cast<const uint8_t*>(src),
+                         reinterpret_cast<uint8_t*>(dst), g);
+      return hipGetLastError();
+    };
+    constexpr int I = IFQ_LAYOUT_I8_NHWC, N = IFQ_LAYOUT_U2_NHWC_PACKED, B = IFQ_LAYOUT_U2_BLOCK64;
+#define IFQ_CONVERT(s, d) \
+  if (src_layout == s && dst_layout == d) return go(convert_units<s, d, 1>, convert_units<s, d, 4>);
+    IFQ_CONVERT(I, N)
+    IFQ_CONVERT(I, B)
+    IFQ_CONVERT(N, I)
+    IFQ_CONVERT(B, I)
+    IFQ_CONVERT(N, B)
+    IFQ_CONVERT(B, N)
+#undef IFQ_CONVERT
+  }
   int64_t blocks = (groups + 255) / 256;
   if (blocks > 65536) blocks = 65536;
   hipLaunchKernelGGL(convert_codes, dim3((unsigned)blocks), dim3(256), 0, stream,

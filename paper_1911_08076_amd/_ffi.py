@@ -6,6 +6,8 @@ is no fallback implementation of any entry point.
 import ctypes
 import os
 
+import numpy as np
+
 HERE = os.path.dirname(os.path.abspath(__file__))
 # always the in-tree build next to this file
 LIB_PATH = os.path.join(HERE, "libifq.so")
@@ -90,6 +92,15 @@ class Stack(ctypes.Structure):
                 ("layers", ctypes.POINTER(Layer)), ("events", vp)]
 
 
+def address(t):
+    """Device or host address of a torch tensor / NumPy array (None -> NULL)."""
+    if t is None:
+        return None
+    if isinstance(t, np.ndarray):
+        return t.ctypes.data
+    return t.data_ptr()
+
+
 # (name, restype, argtypes) of every exported entry point
 SIGNATURES = [
     ("ifq_version", ctypes.c_char_p, []),
@@ -142,12 +153,19 @@ SIGNATURES = [
     ("ifq_static_workspace_bytes", size_t, []),
 ]
 
+# the launching entry points that api.py calls through _ifqcall, in the order
+# its bind() takes their addresses
+CALLED = ["ifq_conv_forward", "ifq_conv_forward_fp4", "ifq_conv_pool_forward",
+          "ifq_conv_pool_forward_fp4", "ifq_maxpool_codes", "ifq_convert_codes",
+          "ifq_run_stack", "ifq_run_stack_static"]
+
 _lib = None
+call = None     # the _ifqcall module, bound to the library
 
 
 def load():
-    """Load libifq.so once; raise ImportError if it is missing."""
-    global _lib
+    """Load libifq.so and _ifqcall.so once; raise ImportError if one is missing."""
+    global _lib, call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -167,5 +185,8 @@ def load():
         fn = getattr(lib, name)
         fn.restype = res
         fn.argtypes = args
+    from . import _ifqcall
+    _ifqcall.bind(address, *[ctypes.cast(getattr(lib, n), vp).value for n in CALLED])
+    call = _ifqcall
     _lib = lib
     return lib

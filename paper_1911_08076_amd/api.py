@@ -1,7 +1,8 @@
 """Python binding of the C ABI: one function per entry point, same names.
 
 Only argument marshalling happens here (descriptors, pointers, the stream
-handle). Every step of the quantized substructure runs in libifq.so: host-side
+handle; the launching calls go through the C extension _ifqcall, the others
+through ctypes). Every step of the quantized substructure runs in libifq.so: host-side
 packing and folding in its C++ code, everything else in its HIP kernels.
 Device tensors are torch tensors; host arrays are NumPy arrays.
 """
@@ -30,22 +31,34 @@ def _check(status, func):
         raise IfqError(status, func, msg)
 
 
-def _ptr(t):
-    """Device or host address of a torch tensor / NumPy array (None -> NULL)."""
-    if t is None:
-        return None
-    if isinstance(t, np.ndarray):
-        return t.ctypes.data
-    return t.data_ptr()
+_ptr = _ffi.address
+
+
+def _struct(v, cls):
+    """Address of the ctypes structure v, which must be a cls."""
+    if not isinstance(v, cls):
+        raise ctypes.ArgumentError("expected %s, got %s" % (cls.__name__, type(v).__name__))
+    return ctypes.addressof(v)
 
 
 def _stream(stream):
     if stream is None:
         import torch
-        return torch.cuda.current_stream().cuda_stream
+        dev = torch.cuda.current_device()      # initialises torch's GPU state if need be
+        return _current_raw_stream(dev)
     if isinstance(stream, int):
         return stream
     return stream.cuda_stream
+
+
+def _current_raw_stream(dev):
+    """torch's current stream on dev as a handle: torch's own raw query where
+    it has one (no Stream object is made), resolved on first use."""
+    global _current_raw_stream
+    import torch
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    _current_raw_stream = raw or (lambda d: torch.cuda.current_stream(d).cuda_stream)
+    return _current_raw_stream(dev)
 
 
 def _f64(a):
@@ -215,16 +228,20 @@ def ifq_conv_forward(desc, x, w_packed, thr, y, join=None, acc_dump=None,
                      ws=None, stream=None):
     """ws None: a zero-filled device workspace of ifq_conv_workspace_bytes
     bytes is made for this call where the layer needs one (a K split)."""
-    if ws is None:
-        need = ifq_conv_workspace_bytes(desc)
-        if need:
-            import torch
-            ws = torch.zeros(need, dtype=torch.uint8, device=y.device)
-    ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    _check(_lib().ifq_conv_forward(
-        ctypes.byref(desc), _ptr(x), _ptr(w_packed), _ptr(thr),
-        None if join is None else ctypes.byref(join), _ptr(y), _ptr(acc_dump),
-        _ptr(ws), ws_bytes, _stream(stream)), "ifq_conv_forward")
+    d = _struct(desc, ConvDesc)
+    j = None if join is None else _struct(join, Join)
+    st = _stream(stream)
+    rc = _ffi.call.conv_forward(d, x, w_packed, thr, j, y, acc_dump, ws, _nbytes(ws), st)
+    if rc == _ffi.IFQ_ERR_INSUFFICIENT_BUFFER and ws is None:
+        import torch
+        ws = torch.zeros(ifq_conv_workspace_bytes(desc), dtype=torch.uint8, device=y.device)
+        rc = _ffi.call.conv_forward(d, x, w_packed, thr, j, y, acc_dump, ws, _nbytes(ws), st)
+    if rc:
+        _check(rc, "ifq_conv_forward")
+
+
+def _nbytes(ws):
+    return 0 if ws is None else ws.numel() * ws.element_size()
 
 
 def ifq_pack_weights_fp4(desc, w_oihw):
@@ -245,21 +262,21 @@ def ifq_conv_fp4_kernel_name(desc, join=None):
 
 
 def ifq_conv_forward_fp4(desc, x, w_fp4, thr, y, join=None, stream=None):
-    _check(_lib().ifq_conv_forward_fp4(
-        ctypes.byref(desc), _ptr(x), _ptr(w_fp4), _ptr(thr),
-        None if join is None else ctypes.byref(join), _ptr(y), _stream(stream)),
+    _check(_ffi.call.conv_forward_fp4(
+        _struct(desc, ConvDesc), x, w_fp4, thr,
+        None if join is None else _struct(join, Join), y, _stream(stream)),
         "ifq_conv_forward_fp4")
 
 
 def ifq_conv_pool_forward(desc, pool, x, w_packed, thr, y, stream=None):
-    _check(_lib().ifq_conv_pool_forward(
-        ctypes.byref(desc), ctypes.byref(pool), _ptr(x), _ptr(w_packed), _ptr(thr),
-        _ptr(y), _stream(stream)), "ifq_conv_pool_forward")
+    _check(_ffi.call.conv_pool_forward(
+        _struct(desc, ConvDesc), _struct(pool, PoolDesc), x, w_packed, thr, y,
+        _stream(stream)), "ifq_conv_pool_forward")
 
 
 def ifq_conv_pool_forward_fp4(desc, pool, x, w_fp4, thr, y, stream=None):
-    _check(_lib().ifq_conv_pool_forward_fp4(
-        ctypes.byref(desc), ctypes.byref(pool), _ptr(x), _ptr(w_fp4), _ptr(thr), _ptr(y),
+    _check(_ffi.call.conv_pool_forward_fp4(
+        _struct(desc, ConvDesc), _struct(pool, PoolDesc), x, w_fp4, thr, y,
         _stream(stream)), "ifq_conv_pool_forward_fp4")
 
 
@@ -272,15 +289,13 @@ def ifq_conv_pool_kernel_name(desc, pool):
 
 
 def ifq_maxpool_codes(desc, x, y, stream=None):
-    _check(_lib().ifq_maxpool_codes(ctypes.byref(desc), _ptr(x), _ptr(y),
-                                    _stream(stream)), "ifq_maxpool_codes")
+    _check(_ffi.call.maxpool_codes(_struct(desc, PoolDesc), x, y, _stream(stream)),
+           "ifq_maxpool_codes")
 
 
 def ifq_convert_codes(n, h, w, c, src_layout, dst_layout, src, dst, stream=None):
-    _check(_lib().ifq_convert_codes(int(n), int(h), int(w), int(c), src_layout,
-                                    dst_layout, _ptr(src), _ptr(dst),
-                                    _stream(stream)),
-           "ifq_convert_codes")
+    _check(_ffi.call.convert_codes(int(n), int(h), int(w), int(c), src_layout, dst_layout,
+                                   src, dst, _stream(stream)), "ifq_convert_codes")
 
 
 def ifq_stack_workspace_bytes(stack):
@@ -296,14 +311,12 @@ def ifq_stack_slot_info(stack, slot):
 
 
 def ifq_run_stack(stack, x, y, ws, stream=None):
-    ws_bytes = 0 if ws is None else ws.numel() * ws.element_size()
-    _check(_lib().ifq_run_stack(ctypes.byref(stack), _ptr(x), _ptr(y),
-                                _ptr(ws), ws_bytes, _stream(stream)),
-           "ifq_run_stack")
+    _check(_ffi.call.run_stack(_struct(stack, Stack), x, y, ws, _nbytes(ws),
+                               _stream(stream)), "ifq_run_stack")
 
 
 def ifq_run_stack_static(stack, x, y, stream=None):
-    _check(_lib().ifq_run_stack_static(ctypes.byref(stack), _ptr(x), _ptr(y), _stream(stream)),
+    _check(_ffi.call.run_stack_static(_struct(stack, Stack), x, y, _stream(stream)),
            "ifq_run_stack_static")
 
 

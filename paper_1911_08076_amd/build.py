@@ -1,4 +1,5 @@
-"""Build libifq.so (HIP for gfx950 + host C++) into this package directory.
+"""Build libifq.so (HIP for gfx950 + host C++) and _ifqcall.so (the CPython
+entry to its launching functions) into this package directory.
 
 Usage: python paper_1911_08076_amd/build.py (runs without importing the
 package, which needs the library to exist)
@@ -6,12 +7,14 @@ package, which needs the library to exist)
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libifq.so")
+CALL = os.path.join(HERE, "_ifqcall.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -58,7 +61,24 @@ def build(verbose=False):
     if r.returncode != 0:
         raise RuntimeError("link failed:\n" + r.stdout + r.stderr)
     os.replace(tmp, LIB)
+    build_call(tag, verbose)
     return LIB
+
+
+def build_call(tag, verbose=False):
+    """The CPython extension (plain C: it holds no device code)."""
+    tmp = CALL + ".tmp" + tag
+    cmd = [os.environ.get("CC", "gcc"), "-O2", "-std=gnu11", "-Wall", "-shared", "-fPIC",
+           "-fvisibility=hidden", "-D__HIP_PLATFORM_AMD__=1",
+           "-I", sysconfig.get_paths()["include"], "-I", INCLUDE,
+           "-I", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
+           os.path.join(CSRC, "ifq_call.c"), "-o", tmp]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError("ifq_call.c failed:\n" + r.stdout + r.stderr)
+    os.replace(tmp, CALL)
 
 
 if __name__ == "__main__":

@@ -678,7 +678,7 @@ int64_t halo_cells_bound(const ConvLaunch& a, int64_t bn) {
 
 }  // namespace
 
-bool plan_halo(const ConvLaunch& a, HaloPlan* out) {
+static bool plan_halo_fit(const ConvLaunch& a, HaloPlan* out) {
   if (!(a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.in_bits == 2 && a.cin % 64 == 0 &&
         a.kh == 3 && a.kw == 3 && a.pad == 1 && (a.stride == 1 || a.stride == 2) && a.m > 0))
     return false;
@@ -767,6 +767,12 @@ const char* conv_halo_name(const HaloPlan& p, const ConvLaunch& a) {
          : inst == 2 ? V.fused_name
          : inst == 1 ? V.sw_name
                      : V.name;
+}
+
+static PlanCache<HaloPlan> g_halo_plans;
+
+bool plan_halo(const ConvLaunch& a, HaloPlan* out) {
+  return g_halo_plans.get(a, out, plan_halo_fit);
 }
 
 hipError_t launch_conv_halo(ConvLaunch a, const HaloPlan& p, hipStream_t stream) {

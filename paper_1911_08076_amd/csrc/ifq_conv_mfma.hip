@@ -32,9 +32,6 @@
 // residual join without cross-lane traffic.
 #include <hip/hip_runtime.h>
 
-#include <cstring>
-#include <mutex>
-
 #include "ifq_epilogue.h"
 #include "ifq_internal.h"
 #include "ifq_mfma_common.h"
@@ -376,12 +373,7 @@ bool mfma_eligible(const ConvLaunch& a) {
 }
 
 // The dispatcher's choice among the three MFMA kernels for one layer, and
-// their plans. Every planner reads only the launch's geometry, layouts,
-// epilogue and K-split fields (no pointer, no quantizer threshold value), so
-// launches with equal values there get the same choice: it is kept in a
-// small table keyed by those fields, which saves the planners' host time
-// (several microseconds per layer, against kernels of ten) on every launch
-// after the first.
+// their plans, kept by layer geometry.
 namespace {
 
 struct MfmaChoice {
@@ -409,53 +401,14 @@ MfmaChoice plan_choice(const ConvLaunch& a) {
   return c;
 }
 
-// The launch with its pointers and threshold values cleared (whether a sum
-// dump is asked for stays a flag); compared byte for byte, so equal keys
-// have equal fields.
-ConvLaunch choice_key(const ConvLaunch& a) {
-  ConvLaunch k;
-  std::memcpy(&k, &a, sizeof(k));
-  k.x = nullptr;
-  k.wgt = nullptr;
-  k.rowsum = nullptr;
-  k.thr = nullptr;
-  k.y = nullptr;
-  k.acc_dump = a.acc_dump ? reinterpret_cast<int32_t*>(alignof(int32_t)) : nullptr;
-  k.shortcut = nullptr;
-  k.coef = nullptr;
-  k.table = nullptr;
-  k.dx = nullptr;
-  k.dwgt = nullptr;
-  k.ws_cnt = nullptr;
-  k.ws_part = nullptr;
-  for (double& q : k.qthr) q = 0.0;
-  return k;
-}
-
-struct ChoiceSlot {
-  bool used;
-  ConvLaunch key;
-  MfmaChoice c;
-};
-constexpr int kChoiceSlots = 256;
-ChoiceSlot g_choice[kChoiceSlots];
-std::mutex g_choice_mu;
+PlanCache<MfmaChoice> g_choice;
 
 MfmaChoice choose_mfma(const ConvLaunch& a) {
-  const ConvLaunch k = choice_key(a);
-  uint64_t hsh = 1469598103934665603ull;   // FNV-1a over the key's bytes
-  const unsigned char* b = reinterpret_cast<const unsigned char*>(&k);
-  for (size_t i = 0; i < sizeof(k); ++i) hsh = (hsh ^ b[i]) * 1099511628211ull;
-  ChoiceSlot& slot = g_choice[hsh % kChoiceSlots];
-  {
-    std::lock_guard<std::mutex> lock(g_choice_mu);
-    if (slot.used && std::memcmp(&slot.key, &k, sizeof(k)) == 0) return slot.c;
-  }
-  const MfmaChoice c = plan_choice(a);
-  std::lock_guard<std::mutex> lock(g_choice_mu);
-  std::memcpy(&slot.key, &k, sizeof(k));
-  slot.c = c;
-  slot.used = true;
+  MfmaChoice c;
+  g_choice.get(a, &c, [](const ConvLaunch& l, MfmaChoice* o) {
+    *o = plan_choice(l);
+    return true;
+  });
   return c;
 }
 

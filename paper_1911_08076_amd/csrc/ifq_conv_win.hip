@@ -39,9 +39,6 @@
 // is 2-3 us of every launch.
 #include <hip/hip_runtime.h>
 
-#include <cstring>
-#include <mutex>
-
 #include "ifq_epilogue.h"
 #include "ifq_internal.h"
 #include "ifq_mfma_common.h"
@@ -824,43 +821,9 @@ bool plan_win(const ConvLaunch& a, WinPlan* out) {
   return found;
 }
 
-// The plan of a layer's geometry, kept per geometry (planning takes a few
-// microseconds; the fields the planner reads are the key).
-struct WinKey {
-  int32_t v[13];
-};
-struct WinSlot {
-  bool used, ok;
-  WinKey key;
-  WinPlan plan;
-};
-constexpr int kWinSlots = 128;
-WinSlot g_win_slots[kWinSlots];
-std::mutex g_win_mu;
+PlanCache<WinPlan> g_win_plans;
 
-bool choose_win(const ConvLaunch& a, WinPlan* out) {
-  const WinKey k = {{a.n, a.h, a.w, a.cin, a.cout, a.kh, a.kw, a.stride, a.pad, a.in_layout,
-                     a.out_mode, a.rec, a.join_kind}};
-  uint64_t hsh = 1469598103934665603ull;
-  for (int32_t x : k.v) hsh = (hsh ^ (uint32_t)x) * 1099511628211ull;
-  WinSlot& slot = g_win_slots[(hsh >> 32) % kWinSlots];
-  {
-    std::lock_guard<std::mutex> lock(g_win_mu);
-    if (slot.used && std::memcmp(&slot.key, &k, sizeof(k)) == 0) {
-      *out = slot.plan;
-      return slot.ok;
-    }
-  }
-  WinPlan p{};
-  const bool ok = plan_win(a, &p);
-  std::lock_guard<std::mutex> lock(g_win_mu);
-  slot.used = true;
-  slot.ok = ok;
-  slot.key = k;
-  slot.plan = p;
-  *out = p;
-  return ok;
-}
+bool choose_win(const ConvLaunch& a, WinPlan* out) { return g_win_plans.get(a, out, plan_win); }
 
 template <int IN>
 hipError_t launch_in(const ConvLaunch& a, const WinPlan& p, hipStream_t stream) {

@@ -1136,7 +1136,7 @@ bool reg3_variant_fp4(int v) {
   return v < w2_variant_count() ? w2_variant_fp4(v) : wp_variant_fp4(v - w2_variant_count());
 }
 
-bool plan_reg3(const ConvLaunch& a, int forced, Reg3Plan* out) {
+static bool plan_reg3_fit(const ConvLaunch& a, int forced, Reg3Plan* out) {
   const int n2 = w2_variant_count();
   if (forced >= 0) {
     out->persistent = forced >= n2;
@@ -1155,6 +1155,15 @@ bool plan_reg3(const ConvLaunch& a, int forced, Reg3Plan* out) {
   out->persistent = wp && (!w2 || out->wp.t_us < out->w2.t_us);
   out->t_us = out->persistent ? out->wp.t_us : out->w2.t_us;
   return true;
+}
+
+static PlanCache<Reg3Plan> g_reg3_plans;
+
+bool plan_reg3(const ConvLaunch& a, int forced, Reg3Plan* out) {
+  if (forced >= 0) return plan_reg3_fit(a, forced, out);
+  return g_reg3_plans.get(a, out, [](const ConvLaunch& l, Reg3Plan* o) {
+    return plan_reg3_fit(l, -1, o);
+  });
 }
 
 hipError_t launch_reg3(const ConvLaunch& a, const Reg3Plan& p, hipStream_t stream) {

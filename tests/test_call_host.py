@@ -1,0 +1,49 @@
+"""The C extension that launches for the binding, on the CPU: argument kinds,
+error status and the workspace retry, with calls that launch nothing."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_1911_08076_amd as P
+from paper_1911_08076_amd import _ffi
+
+X = torch.zeros(64, dtype=torch.uint8)
+THR = torch.zeros(64, 4, dtype=torch.int32)
+
+
+def conv(n=0):
+    return P.conv_desc(n, 28, 28, 64, 64, 3, 1, 1, 2, 2, 3, 3)
+
+
+def test_calls_that_launch_nothing_succeed():
+    P.ifq_conv_forward(conv(), X, X, THR, X, stream=0)
+    P.ifq_conv_forward(conv(), None, None, THR, None, stream=0)
+    P.ifq_maxpool_codes(P.pool_desc(0, 8, 8, 64, 2, 2, 0, 2, 1), X, np.zeros(4, np.uint8),
+                        stream=0)
+    P.ifq_convert_codes(0, 4, 4, 64, 0, 3, X, X, stream=0)
+
+
+def test_status_and_text_reach_the_caller():
+    with pytest.raises(P.IfqError, match="thresholds required") as e:
+        P.ifq_conv_forward(conv(), X, X, None, X, stream=0)
+    assert e.value.status == _ffi.IFQ_ERR_INVALID_ARGUMENT
+    with pytest.raises(P.IfqError, match="layouts"):
+        P.ifq_convert_codes(1, 4, 4, 64, 0, 0, X, X, stream=0)
+    with pytest.raises(P.IfqError, match="need n"):
+        P.ifq_convert_codes(-1, 4, 4, 64, 0, 3, X, X, stream=0)
+
+
+@pytest.mark.parametrize("call,error", [
+    (lambda: P.ifq_maxpool_codes(conv(), X, X, stream=0), ctypes.ArgumentError),
+    (lambda: P.ifq_conv_forward(P.pool_desc(0, 8, 8, 64, 2, 2, 0), X, X, THR, X, stream=0),
+     ctypes.ArgumentError),
+    (lambda: P.ifq_conv_forward(conv(), 4096, X, THR, X, stream=0), AttributeError),
+    (lambda: P.ifq_conv_forward(conv(), X, X, THR, X, join=X, stream=0), ctypes.ArgumentError),
+    (lambda: P.ifq_convert_codes(1, 4, 4, 64, 0.5, 3, X, X, stream=0), TypeError),
+    (lambda: _ffi.call.maxpool_codes(0, X, X), TypeError),
+])
+def test_wrong_kinds_are_refused(call, error):
+    with pytest.raises(error):
+        call()

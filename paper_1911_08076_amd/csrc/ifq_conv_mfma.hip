@@ -84,6 +84,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
   const int rbw = co0 >> 5;                     // first row block
   const int nrb = a.cout_pad >> 5;
   const int howo = a.ho * a.wo;
+  const int ntaps = a.kh * a.kw;
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.wgt) + lane * 16;
   const uint8_t* zero_src = reinterpret_cast<const uint8_t*>(&g_zero_cell);
   const uint32_t lds0 = lds_addr(lds);
@@ -122,9 +123,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
     }
   }
 
-  // Filter tap (r, s) and channel block g of K64 step kk, kept incrementally
-  // (taps fastest): kpos is the position of the first step of the next stage
-  // to issue.
+  // Filter tap (r, s) and channel block g of a K64 step (taps fastest): kept
+  // incrementally from stage to stage where a stage has one or two steps,
+  // else by division (eight steps a stage would walk up to seven on).
+  constexpr bool WALK = SK <= 2;
   struct KPos {
     int g, s, r;
   };
@@ -137,7 +139,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
     q.r = wr ? 0 : q.r;
     q.g += wr ? 1 : 0;
   };
-  KPos kpos{0, 0, 0};
+  KPos kpos{0, 0, 0};             // WALK: the first step of the next stage to issue
 
   // Issue the loads of stage st into ring slot st % D (stages are issued in
   // order). Chunk c covers K64 step kk = st*SK + c / (CA1 + CB1) of the
@@ -159,7 +161,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
         dma16(wbase + off, dst);
       } else {
         KPos q = kpos;
-        for (int u = 0; u < s_; ++u) adv1(q);
+        if constexpr (WALK) {
+          for (int u = 0; u < s_; ++u) adv1(q);
+        } else {
+          q.g = fdiv(kk, a.div_taps);
+          const int tap = kk - q.g * ntaps;
+          q.r = fdiv(tap, a.div_kw);
+          q.s = tap - q.r * a.kw;
+        }
         const int g = q.g, r = q.r, s = q.s;
         const int iy = px_iy0[i] + r;
         const int ix = px_ix0[i] + s;
@@ -170,8 +179,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
         dma16(src, dst);
       }
     }
+    if constexpr (WALK) {
 #pragma unroll
-    for (int u = 0; u < SK; ++u) adv1(kpos);
+      for (int u = 0; u < SK; ++u) adv1(kpos);
+    }
   };
 
   v16i acc[FM][FN];
@@ -316,6 +327,7 @@ const Variant kVariants[] = {
     {2, 4, 1, 1, 2, 9.0, 0.30, "conv_mfma<2, 4, 1, 1, 2, 2, 6>"},    //  64 x 256
     {2, 2, 2, 2, 2, 9.5, 0.309, "conv_mfma<2, 2, 2, 2, 2, 2, 3>"},   // 128 x 128, K split 2
     {2, 1, 4, 1, 4, 6.7, 0.19, "conv_mfma<2, 1, 4, 1, 4, 1, 6>"},    //  64 x 128, K split 4
+    {1, 1, 8, 1, 1, 6.7, 0.19, "conv_mfma<1, 1, 8, 1, 1, 1, 6>"},    //  32 x 32, K split 8
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kNumCUs = 256;
@@ -359,6 +371,8 @@ Plan plan_mfma(const ConvLaunch& a) {
 template <int WM, int WN, int WK, int FM, int FN, int S, int D>
 hipError_t launch_variant(ConvLaunch a, const Plan& pl, hipStream_t stream) {
   a.bn = pl.bn;
+  a.div_taps = make_fastdiv(a.kh * a.kw);
+  a.div_kw = make_fastdiv(a.kw);
   dim3 grid(pl.blocks_m, (a.cout + 32 * FM * WM - 1) / (32 * FM * WM));
   hipLaunchKernelGGL((conv_mfma<WM, WN, WK, FM, FN, S, D>), grid,
                      dim3(64 * WM * WN * WK), 0, stream, a);
@@ -377,11 +391,21 @@ bool mfma_eligible(const ConvLaunch& a) {
 namespace {
 
 struct MfmaChoice {
-  int kind;   // 0 register-blocked (reg3), 1 windowed, 2 tiled, -1 none
+  int kind;   // 0 register-blocked (reg3), 1 windowed 3x3, 2 tiled, 3 windowed, -1 none
   HaloPlan hp;
   Reg3Plan rp;
   Plan pl;
 };
+
+// Layers the windowed kernel of ifq_conv_win.hip is weighed for. Not 3x3
+// layers on BLOCK64 codes, which the register-blocked kernels take (batch 7,
+// 72x56x192 -> 128: 9.7 us against 12.3), and not fully connected layers: one
+// output pixel per image shares no window with another, and the tiled
+// kernel's deeper ring streams their weights faster.
+bool win_candidate(const ConvLaunch& a) {
+  if (a.ho * a.wo == 1) return false;
+  return !(a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3);
+}
 
 MfmaChoice plan_choice(const ConvLaunch& a) {
   MfmaChoice c{};
@@ -398,6 +422,13 @@ MfmaChoice plan_choice(const ConvLaunch& a) {
     c.kind = 1;
   else
     c.kind = 2;
+  // by a margin: the tiled kernel's prediction is high on its largest tiles
+  // (64x56x56x64 -> 64 3x3 packed: 26.6 us predicted, 23.9 measured, against
+  // 25.6 and 26.3 for the windowed kernel)
+  double tw = 0;
+  if (win_candidate(a) && plan_win_us(a, &tw) &&
+      tw < 0.85 * (c.kind == 0 ? c.rp.t_us : c.kind == 1 ? c.hp.t_us : c.pl.t_us))
+    c.kind = 3;
   return c;
 }
 
@@ -424,6 +455,7 @@ const char* conv_mfma_name(const ConvLaunch& a) {
   const MfmaChoice c = choose_mfma(a);
   if (c.kind == 0) return reg3_name(c.rp, a);
   if (c.kind == 1) return conv_halo_name(c.hp, a);
+  if (c.kind == 3) return conv_win_name(a);
   if (c.kind < 0) return "";
   return kVariants[c.pl.variant].name;
 }
@@ -439,6 +471,7 @@ hipError_t launch_conv_mfma(const ConvLaunch& a, hipStream_t stream) {
   const MfmaChoice c = choose_mfma(a);
   if (c.kind == 0) return launch_reg3(a, c.rp, stream);
   if (c.kind == 1) return launch_conv_halo(a, c.hp, stream);
+  if (c.kind == 3) return launch_conv_win(a, stream);
   if (c.kind < 0) return hipErrorNotSupported;
   const Plan& pl = c.pl;
   switch (pl.variant) {
@@ -447,7 +480,8 @@ hipError_t launch_conv_mfma(const ConvLaunch& a, hipStream_t stream) {
     case 2: return launch_variant<1, 8, 1, 2, 2, 2, 4>(a, pl, stream);
     case 3: return launch_variant<2, 4, 1, 1, 2, 2, 6>(a, pl, stream);
     case 4: return launch_variant<2, 2, 2, 2, 2, 2, 3>(a, pl, stream);
-    default: return launch_variant<2, 1, 4, 1, 4, 1, 6>(a, pl, stream);
+    case 5: return launch_variant<2, 1, 4, 1, 4, 1, 6>(a, pl, stream);
+    default: return launch_variant<1, 1, 8, 1, 1, 1, 6>(a, pl, stream);
   }
 }
 

@@ -17,7 +17,8 @@
 //  - Weights stream through a ring of D stages of SK = S*WK K64 steps, one
 //    barrier a stage. K runs over (chunk, tap, unit): the row-major weight
 //    blob's 16-byte units are gathered in that order by the DMA's per-lane
-//    addresses, four lanes to a row, so the blob needs no layout of its own.
+//    addresses, four lanes to a row, so the blob needs no layout of its own
+//    (with c_in % 64 == 0 on 2-bit codes it is in fragment order, 1 KB spans).
 //  - Small layers (a few hundred pixels, K in the thousands) leave most CUs
 //    idle on wide tiles: tiles down to 32 x 32 exist with WK = 4 or 8 wave
 //    groups splitting the K64 steps of a stage, their sums added in LDS by
@@ -49,10 +50,11 @@ namespace {
 enum WinIn {
   kWinI8 = 0,   // byte codes: a cell is 16 bytes, one unit of 16 channels
   kWinU2 = 1,   // 2-bit packed codes: a cell is 4 bytes, one unit
-};
+  kWinF = 2,    // 2-bit codes, c_in % 64 == 0, weights in MFMA fragment order
+};              // (mfma_layout): a cell is 16 bytes, 64 channels, a K64 step of a tap
 
 struct WinGeom {
-  int32_t u;          // units (16 channels) per window pixel and chunk
+  int32_t u;          // cells per window pixel and chunk
   int32_t nch;        // chunks (the last one may hold fewer units)
   int32_t nbuf;       // window buffers
   int32_t nks;        // K64 steps per chunk (the last one padded with zeros)
@@ -61,7 +63,7 @@ struct WinGeom {
   int32_t rimg;       // window rows of a whole image
   int32_t wcells;     // cells per buffer, a multiple of 64
   int32_t one;        // 1x1 filter: the window's pixels are the tile's own
-  int32_t sh, msk;    // window swizzle: unit c of pixel q at c ^ ((q >> sh) & msk)
+  int32_t sh, msk;    // window swizzle: cell c of pixel q at c ^ ((q >> sh) & msk)
   int32_t ring_off, win_off, tab_off;   // LDS offsets past the epilogue's parameters
   int32_t ktab_off;
   int32_t red_off, out_off;             // after the main loop: K-group sums, output tile
@@ -280,7 +282,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
   constexpr int C = SK * CA1;
   static_assert(C % NW == 0, "equal loads per wave");
   constexpr int CPW = C / NW;
-  constexpr int CB = IN == kWinI8 ? 16 : 4;     // bytes per window cell
+  constexpr int CB = IN == kWinU2 ? 4 : 16;     // bytes per window cell
+  constexpr bool FR = IN == kWinF;
+  constexpr int E = FR ? 1 : 4;                 // cells of a K64 step
   extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
   const int tid = threadIdx.x;
@@ -295,7 +299,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
   const int p0 = blockIdx.x * g.bn;
   const int co0 = blockIdx.y * BM;
   const int npx = a.m - p0 < g.bn ? a.m - p0 : g.bn;   // pixels of the tile
-  const int cg16 = a.cin >> 4;
+  const int cgt = a.cin >> (FR ? 6 : 4);        // cells of an input pixel
+  const bool b64 = FR && a.in_layout == IFQ_LAYOUT_U2_BLOCK64;
+  const int hw = a.h * a.w;
   const int ntaps = a.kh * a.kw;
   const int nst = (g.nkk + SK - 1) / SK;
   const int howo = a.ho * a.wo;
@@ -304,7 +310,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
   const uint32_t ring0 = lds0 + g.ring_off, win0 = lds0 + g.win_off;
   int32_t* wtab = reinterpret_cast<int32_t*>(lds + g.tab_off);
   int2* ktab_b = reinterpret_cast<int2*>(lds + g.ktab_off);
-  int32_t* ktab_a = reinterpret_cast<int32_t*>(ktab_b + nst * SK * 4);
+  int32_t* ktab_a = reinterpret_cast<int32_t*>(ktab_b + nst * SK * E);
   int32_t* unsorted = reinterpret_cast<int32_t*>(lds + g.ring_off - 16);   // past the parameters
   const uint8_t* zero_src = reinterpret_cast<const uint8_t*>(&g_zero_cell);
 
@@ -349,26 +355,28 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
       }
     }
     const bool ok = (unsigned)iy < (unsigned)a.h && (unsigned)ix < (unsigned)a.w;
-    wtab[q] = ok ? ((img * a.h + iy) * a.w + ix) * cg16 : -1;
+    const int px = iy * a.w + ix;
+    wtab[q] = !ok ? -1 : b64 ? img * cgt * hw + px : (img * hw + px) * cgt;
   }
   if (tid == NT2) wtab[wpx] = -1;
 
-  // unit 4*kk + j of the K order -> its byte in a weight row (-1: padding of
-  // the K64 step, zero weights), its window's byte offset (buffer, tap) and
-  // tap offset in pixels | unit in the pixel << 16 for the swizzle
-  for (int i = tid; tid < NT2 && i < nst * SK * 4; i += NT2) {
-    int kk = i >> 2;
+  // cell E*kk + j of the K order -> its byte in a weight row, or in a row
+  // block's fragments (-1: padding of K, zero weights), its window's byte
+  // offset (buffer, tap) and tap offset in pixels | cell in the pixel << 16
+  // for the swizzle
+  for (int i = tid; tid < NT2 && i < nst * SK * E; i += NT2) {
+    int kk = i / E;
     const bool past = kk >= g.nkk;
     if (past) kk = g.nkk - 1;
     const int ch = fdiv(kk, g.div_nks);
-    const int un = 4 * (kk - ch * g.nks) + (i & 3);
+    const int un = E * (kk - ch * g.nks) + (i & (E - 1));
     const int tap = fdiv(un, g.div_u);
     const int cu = un - tap * g.u;
-    const bool ok = !past && tap < ntaps && ch * g.u + cu < cg16;
+    const bool ok = !past && tap < ntaps && ch * g.u + cu < cgt;
     const int c = ok ? cu : 0;
     const int r = fdiv(tap, g.div_kw);
     const int off = ok ? r * g.win + (tap - r * a.kw) : 0;
-    ktab_a[i] = ok ? (tap * cg16 + ch * g.u + c) * 16 : -1;
+    ktab_a[i] = !ok ? -1 : FR ? ((ch * g.u + c) * ntaps + tap) * 2048 : (tap * cgt + ch * g.u + c) * 16;
     ktab_b[i] = int2{off * pitch + (ch % g.nbuf) * g.wcells * CB, off | (c << 16)};
   }
   if (tid == 0) *unsorted = 0;
@@ -399,7 +407,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
   // a time; returns this wave's count of loads.
   auto issue_win = [&](int ch) {
     const uint32_t wb = win0 + (uint32_t)((ch % g.nbuf) * g.wcells * CB);
-    const uint8_t* xc = a.x + (int64_t)ch * g.u * CB;
+    const int cstr = b64 ? hw : 1;               // cells between a pixel's channel blocks
+    const uint8_t* xc = a.x + (int64_t)ch * g.u * cstr * CB;
     int cnt = 0;
     for (int i0 = wave; i0 < ncw; i0 += 4 * NW) {
       int cell[4], c[4];
@@ -414,9 +423,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
       for (int k = 0; k < 4; ++k) {
         const int i = i0 + k * NW;
         if (i >= ncw) break;
-        const bool none = cell[k] < 0 || ch * g.u + c[k] >= cg16;
-        const uint8_t* src = none ? zero_src : xc + (uint32_t)(cell[k] + c[k]) * CB;
-        if constexpr (IN == kWinI8) dma16(src, wb + (uint32_t)i * 1024);
+        const bool none = cell[k] < 0 || ch * g.u + c[k] >= cgt;
+        const uint8_t* src = none ? zero_src : xc + (uint32_t)(cell[k] + c[k] * cstr) * CB;
+        if constexpr (CB == 16) dma16(src, wb + (uint32_t)i * 1024);
         else dma4(src, wb + (uint32_t)i * 256);
         ++cnt;
       }
@@ -425,9 +434,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
   };
 
   // The wave's weight loads: 1 KB chunk wave + NW*i of a stage is 16 rows of
-  // one K64 step, four lanes to a row; slot j of row r holds unit
-  // j ^ ((r >> 2) & 3). Rows are fixed; the unit's byte comes from the table,
-  // read a stage ahead.
+  // one K64 step, four lanes to a row, slot j of row r holding unit
+  // j ^ ((r >> 2) & 3); in fragment order a K32 half of 32 rows as it is.
+  // Rows are fixed; the unit's byte comes from the table, read a stage ahead.
   int arow[CPW], aent[CPW], anext[CPW];
   const int azero = (int)a.wzero + lane * 16;
 #pragma unroll
@@ -435,15 +444,21 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
     const int c = wave + NW * i;
     const int s_ = c / CA1;
     const int rg = c - s_ * CA1;
-    const int row = rg * 16 + (lane >> 2);
-    arow[i] = co0 + rg * 16 < a.cout_pad ? (co0 + row) * a.kpad : -1;
-    aent[i] = s_ * 4 + ((lane & 3) ^ ((row >> 2) & 3));
+    if constexpr (FR) {
+      const int rb = (co0 >> 5) + (rg >> 1);
+      arow[i] = rb * 32 < a.cout_pad ? (rb * 2 * a.nk + (rg & 1)) * 1024 + lane * 16 : -1;
+      aent[i] = s_;
+    } else {
+      const int row = rg * 16 + (lane >> 2);
+      arow[i] = co0 + rg * 16 < a.cout_pad ? (co0 + row) * a.kpad : -1;
+      aent[i] = s_ * 4 + ((lane & 3) ^ ((row >> 2) & 3));
+    }
     anext[i] = ktab_a[aent[i]];
   }
   // Weight chunk i of stage st into ring slot st % D (stages in order).
   auto issue_a = [&](int st, int i) {
     const uint32_t slot = ring0 + (uint32_t)((st % D) * STAGE);
-    const int nx = st + 1 < nst ? (st + 1) * SK * 4 : 0;
+    const int nx = st + 1 < nst ? (st + 1) * SK * E : 0;
     const int off = (anext[i] | arow[i]) < 0 ? azero : arow[i] + anext[i];
     dma16s(a.wgt, (uint32_t)off, slot + (uint32_t)(wave + NW * i) * 1024);
     anext[i] = ktab_a[nx + aent[i]];
@@ -455,22 +470,27 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
 #pragma unroll
     for (int fn = 0; fn < FN; ++fn) acc[fm][fn] = v16i{0};
 
-  // the lane's weight fragments of K32 step t (units 2t + h): row l32 of each block
+  // the lane's weight fragments of K32 step t (units 2t + h): row l32 of each
+  // block; in fragment order 1 KB a block and K32 step
+  constexpr int ABLK = FR ? 2048 : 32 * 64;      // bytes between 32-row blocks
   int aoff[2];
 #pragma unroll
   for (int t = 0; t < 2; ++t)
-    aoff[t] = (wm * FM * 32 + l32) * 64 + (((2 * t + h) ^ ((l32 >> 2) & 3)) << 4);
+    aoff[t] = wm * FM * ABLK + (FR ? t * 1024 + lane * 16
+                                   : l32 * 64 + (((2 * t + h) ^ ((l32 >> 2) & 3)) << 4));
 
   int pbp[FN];
 #pragma unroll
   for (int fn = 0; fn < FN; ++fn) pbp[fn] = __umul24(pb[fn], pitch) + g.win_off;
-  // the window offsets of a wave's K32 steps of a stage
-  const int2* kb = ktab_b + kg * S * 4 + h;
-  int2 bnext[S][2];
+  // the window offsets of a wave's K32 steps of a stage (of its K64 steps
+  // where a cell holds both halves)
+  constexpr int NT = FR ? 1 : 2;
+  const int2* kb = ktab_b + kg * S * E + (FR ? 0 : h);
+  int2 bnext[S][NT];
 #pragma unroll
   for (int s_ = 0; s_ < S; ++s_)
 #pragma unroll
-    for (int t = 0; t < 2; ++t) bnext[s_][t] = kb[s_ * 4 + 2 * t];
+    for (int t = 0; t < NT; ++t) bnext[s_][t] = kb[s_ * E + 2 * t];
 
   // One stage. The weight loads of stage st + D - 1 are issued between the
   // MFMA groups: the eight waves' loads queue at the CU's one address unit
@@ -482,41 +502,44 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
     const bool more = st + D - 1 < nst;
     v4i af[NSUB][FM], bf[NSUB][FN];
     uint32_t braw[NSUB][FN];
+    const int nx = st + 1 < nst ? (st + 1) * SK * E : 0;
+    // fragments of K32 step j; a step's table entries are refilled for the
+    // next stage once its last half has used them
     auto load = [&](int j) {
       const int s_ = j >> 1, t = j & 1;
-      const int2 e = bnext[s_][t];
 #pragma unroll
       for (int fm = 0; fm < FM; ++fm)
-        af[j][fm] = *reinterpret_cast<const v4i*>(as + s_ * A_STEP + aoff[t] + fm * 32 * 64);
+        af[j][fm] = *reinterpret_cast<const v4i*>(as + s_ * A_STEP + aoff[t] + fm * ABLK);
+      if (!FR || t == 0) {
+        const int2 e = bnext[s_][FR ? 0 : t];
 #pragma unroll
-      for (int fn = 0; fn < FN; ++fn) {
-        const int sw = ((pb[fn] + (e.y & 0xFFFF)) >> g.sh) & g.msk;
-        const uint8_t* src = lds + pbp[fn] + e.x + ((e.y >> 16) ^ sw) * CB;
-        if constexpr (IN == kWinI8) bf[j][fn] = *reinterpret_cast<const v4i*>(src);
-        else braw[j][fn] = *reinterpret_cast<const uint32_t*>(src);
+        for (int fn = 0; fn < FN; ++fn) {
+          const int sw = ((pb[fn] + (e.y & 0xFFFF)) >> g.sh) & g.msk;
+          const uint8_t* src = lds + pbp[fn] + e.x + ((e.y >> 16) ^ sw) * CB;
+          if constexpr (IN == kWinI8) {
+            bf[j][fn] = *reinterpret_cast<const v4i*>(src);
+          } else if constexpr (FR) {
+            const v2i r = *reinterpret_cast<const v2i*>(src + 8 * h);
+            braw[j][fn] = (uint32_t)r.x;
+            braw[j + 1][fn] = (uint32_t)r.y;
+          } else {
+            braw[j][fn] = *reinterpret_cast<const uint32_t*>(src);
+          }
+        }
+      }
+      if (t == 1) {
+#pragma unroll
+        for (int q = 0; q < NT; ++q) bnext[s_][q] = kb[nx + s_ * E + 2 * q];
       }
     };
     load(0);
-    if constexpr (NSUB > 1) load(1);
-    const int nx = st + 1 < nst ? (st + 1) * SK * 4 : 0;
-#pragma unroll
-    for (int s_ = 0; s_ < S; ++s_)
-      if (2 * s_ < 2) {
-        bnext[s_][0] = kb[nx + s_ * 4];
-        bnext[s_][1] = kb[nx + s_ * 4 + 2];
-      }
+    load(1);
 #pragma unroll
     for (int j = 0; j < NSUB; ++j) {
-      if (j > 0 && j + 1 < NSUB) {
-        load(j + 1);
-        if ((j + 1) & 1) {
-          bnext[(j + 1) >> 1][0] = kb[nx + ((j + 1) >> 1) * 4];
-          bnext[(j + 1) >> 1][1] = kb[nx + ((j + 1) >> 1) * 4 + 2];
-        }
-      }
+      if (j > 0 && j + 1 < NSUB) load(j + 1);
 #pragma unroll
       for (int fn = 0; fn < FN; ++fn) {
-        if constexpr (IN == kWinU2) bf[j][fn] = unpack2(braw[j][fn]);
+        if constexpr (IN != kWinI8) bf[j][fn] = unpack2(braw[j][fn]);
 #pragma unroll
         for (int fm = 0; fm < FM; ++fm)
           acc[fm][fn] =
@@ -667,12 +690,13 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_win(ConvLaunch a, WinG
 // ---- Variants and planning --------------------------------------------------
 struct WinVariant {
   int wm, wn, wk, fm, fn, s, d;
-  const char* name[2];
+  const char* name[3];
 };
 #define IFQ_WV(wm, wn, wk, fm, fn, s, d)                                        \
   {wm, wn, wk, fm, fn, s, d,                                                     \
    {"conv_win<0, " #wm ", " #wn ", " #wk ", " #fm ", " #fn ", " #s ", " #d ">",  \
-    "conv_win<1, " #wm ", " #wn ", " #wk ", " #fm ", " #fn ", " #s ", " #d ">"}}
+    "conv_win<1, " #wm ", " #wn ", " #wk ", " #fm ", " #fn ", " #s ", " #d ">",  \
+    "conv_win<2, " #wm ", " #wn ", " #wk ", " #fm ", " #fn ", " #s ", " #d ">"}}
 const WinVariant kWin[] = {
     IFQ_WV(2, 4, 1, 2, 2, 2, 3),   // 128 x 256, K split 1
     IFQ_WV(2, 2, 2, 2, 1, 2, 3),   // 128 x 64, K split 2
@@ -687,7 +711,9 @@ const WinVariant kWin[] = {
 constexpr int kNumWin = sizeof(kWin) / sizeof(kWin[0]);
 constexpr int kWinLds = 160 * 1024;
 
-int win_in(const ConvLaunch& a) { return a.in_layout == IFQ_LAYOUT_I8_NHWC ? kWinI8 : kWinU2; }
+int win_in(const ConvLaunch& a) {
+  return a.in_layout == IFQ_LAYOUT_I8_NHWC ? kWinI8 : a.cin % 64 ? kWinU2 : kWinF;
+}
 
 struct WinPlan {
   int variant;
@@ -716,7 +742,8 @@ int64_t win_rows_bound(const ConvLaunch& a, int64_t bn) {
 bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
   const WinVariant& V = kWin[v];
   const int bm = 32 * V.fm * V.wm, bnmax = 32 * V.fn * V.wn, sk = V.s * V.wk;
-  const int cb = win_in(a) == kWinI8 ? 16 : 4;
+  const bool fr = win_in(a) == kWinF;
+  const int cb = win_in(a) == kWinU2 ? 4 : 16, e = fr ? 1 : 4;
   const int64_t nco = (a.cout + bm - 1) / bm;
   const int64_t nb_min = (a.m + bnmax - 1) / bnmax;
   const int64_t rounds = (nco * nb_min + kPlanCUs - 1) / kPlanCUs;
@@ -724,11 +751,11 @@ bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
   if (nb < nb_min) nb = nb_min;
   int64_t bn = ((a.m + nb - 1) / nb + 31) / 32 * 32;
   if (bn > bnmax) bn = bnmax;
-  const int cg16 = a.cin / 16, ntaps = a.kh * a.kw;
+  const int cgt = a.cin / (fr ? 64 : 16), ntaps = a.kh * a.kw;   // cells per pixel, taps
   const bool one = ntaps == 1;
   const int64_t wincols = one ? 1 : (int64_t)(a.wo - 1) * a.stride + a.kw;
   const int64_t wpx = one ? bn : win_rows_bound(a, bn) * wincols;
-  if (wpx * cg16 >= (1 << 23) || wpx >= (1 << 15)) return false;   // table fields
+  if (wpx * cgt >= (1 << 23) || wpx >= (1 << 15)) return false;   // table fields
   const int prm = (win_param_bytes(a, bm) + 16 + 1023) / 1024 * 1024;
   const int ring = V.d * sk * bm * 64;
   const int64_t tab = (wpx * 4 + 4 + 1023) / 1024 * 1024;
@@ -740,16 +767,16 @@ bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
   // fits), or all channels at once; chunks of whole 64-byte spans of the
   // weight rows where c_in allows it
   const int kPad[] = {104, 116, 160};
-  for (int pass = 0; pass < 3 * cg16; ++pass) {
-    const int u = pass % cg16 + 1;
-    if (cg16 % 4 == 0 && u % 4) continue;
-    const int nch = (cg16 + u - 1) / u;
-    const int nks = (ntaps * u + 3) / 4;
+  for (int pass = 0; pass < 3 * cgt; ++pass) {
+    const int u = pass % cgt + 1;
+    if (!fr && cgt % 4 == 0 && u % 4) continue;
+    const int nch = (cgt + u - 1) / u;
+    const int nks = (ntaps * u + e - 1) / e;
     if (nch > 1 && (nks < V.d * sk ||
-                    (int64_t)400 * nks * nch > (int64_t)kPad[pass / cg16] * ntaps * cg16))
+                    (int64_t)100 * e * nks * nch > (int64_t)kPad[pass / cgt] * ntaps * cgt))
       continue;
     const int64_t wcells = (wpx * u + 63) / 64 * 64;
-    const int64_t ktab = ((int64_t)(nch * nks + sk - 1) / sk * sk * 48 + 1023) / 1024 * 1024;
+    const int64_t ktab = ((int64_t)(nch * nks + sk - 1) / sk * sk * 12 * e + 1023) / 1024 * 1024;
     const int64_t room = kWinLds - prm - ring - tab - ktab;
     const int64_t fitb = room / (wcells * cb);
     if (fitb < (nch > 1 ? 2 : 1)) continue;
@@ -791,19 +818,30 @@ bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
     // predicted time in clocks of a tile: prologue and window loads, stages
     // (barrier and latency, matrix cores, weights through the address unit),
     // K-group sums, epilogue; two tiles on a CU at once where LDS holds two
-    // cost 1.28 of one. Fitted to 620 measured (layer, variant) times over 65
-    // byte and 2-bit layers (9% rms; its choice 2% slower than the best one).
+    // cost 1.28 (1.36) of one. Fitted to 620 measured (layer, variant) times
+    // over 65 byte and 2-bit layers, and to 390 over 45 in fragment order (9%
+    // rms both; the choice is 2% slower than the best one).
     const int64_t tiles = nco * ((a.m + bn - 1) / bn);
     const int64_t per_cu = (tiles + kPlanCUs - 1) / kPlanCUs;
     const int nst = (g.nkk + sk - 1) / sk;
     const double loads = (double)(nch * wcells) / 64 / 8;
     const double outs = (double)bm * bnmax;
-    const double lv = a.rec == 8 || a.rec == 16 ? 3.0 : a.rec == 2 ? 1.5 : 1.0;
-    const double one_clk = 4650 + 276 * loads + nst * (506 + 1.06 * outs * sk / 64 + 0.62 * bm * sk) +
-                           3.26 * (V.wk - 1) * outs * 4 / 200 + 85 * lv * outs / 512;
-    const double clk = 2 * total <= kWinLds ? (per_cu / 2 * 1.28 + per_cu % 2) * one_clk
-                                            : per_cu * one_clk;
-    out->t_us = 1.5 + clk / 2150;
+    const double red = (V.wk - 1) * outs * 4 / 200;
+    double one_clk, pair, t0;
+    if (fr) {
+      const double epi = a.out_mode == 0 ? 215 : a.join_kind ? 221 : 118;
+      one_clk = 2360 + 943 * loads + nst * (497 + 1.07 * outs * sk / 64 + 0.65 * bm * sk) +
+                6.76 * red + epi * outs / 512;
+      pair = 1.36;
+      t0 = 2.35;
+    } else {
+      const double lv = a.rec == 8 || a.rec == 16 ? 3.0 : a.rec == 2 ? 1.5 : 1.0;
+      one_clk = 4650 + 276 * loads + nst * (506 + 1.06 * outs * sk / 64 + 0.62 * bm * sk) +
+                3.26 * red + 85 * lv * outs / 512;
+      pair = 1.28;
+      t0 = 1.5;
+    }
+    out->t_us = t0 + (2 * total <= kWinLds ? (per_cu / 2) * pair + per_cu % 2 : per_cu) * one_clk / 2150;
     return true;
   }
   return false;
@@ -857,10 +895,18 @@ bool win_eligible(const ConvLaunch& a) {
     if (a.in_bits == 8 || ((uintptr_t)a.x & 15)) return false;
   } else if (a.in_layout != IFQ_LAYOUT_U2_NHWC_PACKED || a.cin % 64 == 0 ||
              ((uintptr_t)a.x & 3)) {
-    return false;
+    return false;   // c_in % 64 == 0: the MFMA dispatcher's choice (plan_win)
   }
   WinPlan p;
   return choose_win(a, &p);
+}
+
+bool plan_win_us(const ConvLaunch& a, double* t_us) {
+  WinPlan p;
+  if (a.m <= 0 || a.pool_k || a.join_kind == IFQ_JOIN_CONV_FUSED || a.f4 || !choose_win(a, &p))
+    return false;
+  *t_us = p.t_us;
+  return true;
 }
 
 const char* conv_win_name(const ConvLaunch& a) {
@@ -871,7 +917,11 @@ const char* conv_win_name(const ConvLaunch& a) {
 hipError_t launch_conv_win(const ConvLaunch& a, hipStream_t stream) {
   WinPlan p;
   if (!choose_win(a, &p)) return hipErrorNotSupported;
-  return win_in(a) == kWinI8 ? launch_in<kWinI8>(a, p, stream) : launch_in<kWinU2>(a, p, stream);
+  switch (win_in(a)) {
+    case kWinI8: return launch_in<kWinI8>(a, p, stream);
+    case kWinU2: return launch_in<kWinU2>(a, p, stream);
+    default: return launch_in<kWinF>(a, p, stream);
+  }
 }
 
 }  // namespace ifq

@@ -131,6 +131,8 @@ struct ConvLaunch {
   int32_t pho, pwo;
   FastDiv div_pwo;     // division by pwo (pooled pixel -> pooled row)
   FastDiv div_pho;     // division by pho (pooled row -> image)
+  FastDiv div_taps;    // tiled kernel: division by kh*kw (K64 step -> channel block)
+  FastDiv div_kw;      // and by kw (tap -> row)
   int32_t wcells;      // register-blocked 3x3 kernels: window cells per channel block
   int32_t tiles_wg;    // persistent 3x3 kernel: consecutive pixel tiles per workgroup
   // K split across workgroups (register-blocked 3x3 kernel, threshold
@@ -385,6 +387,9 @@ inline bool fused_supported(const ConvLaunch& a) {
 bool win_eligible(const ConvLaunch& a);
 hipError_t launch_conv_win(const ConvLaunch& a, hipStream_t stream);
 const char* conv_win_name(const ConvLaunch& a);
+// Its predicted time on 2-bit codes with c_in a multiple of 64 (either 2-bit
+// layout), where it takes the layer.
+bool plan_win_us(const ConvLaunch& a, double* t_us);
 
 // 8-bit input codes with c_in <= 4 (a detector's first layer): whether the
 // small-channel kernel takes the layer, its launch and its name.

@@ -1,5 +1,5 @@
-"""GPU parity of the windowed kernel for byte codes and 2-bit NHWC codes
-(conv_win): int32 sums and codes equal to the oracle's bit for bit, at the
+"""GPU parity of the windowed kernel for byte codes and 2-bit codes of any
+filter size (conv_win): int32 sums and codes equal to the oracle's bit for bit, at the
 edges of its tiles, window chunks and epilogues."""
 import zlib
 
@@ -49,6 +49,15 @@ CASES = [
     ("u2_5x5", 3, 27, 27, 96, 256, 5, 1, 2, 2, 2, U2, B64),
     ("u2_k_bits_out", 2, 9, 9, 48, 70, 3, 1, 1, 2, 4, U2, I8),
     ("u2_i32", 2, 9, 9, 176, 30, 1, 1, 0, 2, 0, U2, I32),
+    # weights in fragment order (c_in % 64 == 0), both 2-bit layouts
+    ("f_3x3_s2", 6, 75, 57, 128, 160, 3, 2, 1, 2, 2, U2, U2),
+    ("f_images_per_tile", 9, 7, 7, 512, 512, 3, 1, 1, 2, 2, U2, B64),
+    ("f_5x5_blocks", 4, 27, 27, 128, 256, 5, 1, 2, 2, 2, B64, B64),
+    ("f_5x5_s2", 2, 112, 86, 64, 330, 5, 2, 2, 2, 2, B64, I8),
+    ("f_1x1_blocks", 5, 19, 23, 320, 192, 1, 2, 0, 2, 2, B64, U2),
+    ("f_1x1_i32", 8, 16, 12, 64, 193, 1, 1, 0, 2, 0, B64, I32),
+    ("f_wide", 9, 60, 52, 128, 448, 5, 2, 2, 2, 2, B64, B64),
+    ("f_even_filter", 3, 20, 18, 192, 48, 4, 1, 2, 2, 4, U2, I8),
 ]
 
 
@@ -58,7 +67,7 @@ def test_conv_win_bit_exact(P, case, dump):
     name, n, h, w, cin, cout, k, st, pad, ib, ob, il, ol = case
     L = make_layer(name, h, w, cin, cout, k, st, pad, ib, ob)
     d = P.conv_desc(n, h, w, cin, cout, k, st, pad, ib, ob, il, ol)
-    assert P.ifq_conv_kernel_name(d).startswith("conv_win<")
+    assert P.ifq_conv_kernel_name(d).startswith("conv_win<"), P.ifq_conv_kernel_name(d)
     seed = zlib.crc32(name.encode()) % 983
     p = params_for(seed, L)
     x = codes_for(seed, (n, h, w, cin), ib)
@@ -79,6 +88,18 @@ def test_conv_win_identity_join(P, ob, ol, sl):
     acc, got = gpu_layer(P, L, 3, x, p, in_layout=I8, out_layout=ol, shortcut=sc, sc_layout=sl)
     assert np.array_equal(acc, want_acc)
     assert np.array_equal(got, expect_layout(want, ol))
+
+
+def test_conv_win_identity_join_fragment_order(P):
+    L = make_layer("join", 13, 11, 128, 192, 3, 1, 1, 2, 2, join=("identity", "x"))
+    p = params_for(13, L)
+    x = codes_for(13, (7, 13, 11, 128), 2)
+    sc = codes_for(14, (7, 13, 11, 192), 2)
+    want_acc, want = oracle_layer(L, x, p, shortcut=sc)
+    for sl in (U2, B64, I8):
+        acc, got = gpu_layer(P, L, 7, x, p, in_layout=U2, out_layout=U2, shortcut=sc, sc_layout=sl)
+        assert np.array_equal(acc, want_acc)
+        assert np.array_equal(got, expect_layout(want, U2))
 
 
 def test_conv_win_conv_join(P):

@@ -307,6 +307,173 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
   copy_out_tile(a, otile, orow, co0, BM, p0, npx);
 }
 
+// Fully connected layers: one filter window covering the whole image (kh == h,
+// kw == w, no padding), so a layer is a product of n pixels with a weight
+// matrix that is read once. AlexNet's first one is 38 MB of weights for 32
+// images: HBM bounds it, and what it needs is many bytes in flight from every
+// CU. A workgroup takes 16 output channels (256 workgroups for 4096) and 16*NB
+// images; its eight waves split the groups of four K64 steps, each loading
+// weight fragments and codes straight into registers, two batches of U groups
+// ahead of the MFMAs (v_mfma_i32_16x16x64_i8), with no LDS and no barrier
+// until the sums are added. Lane 16*q + r takes step q of a group for weight
+// row and image r, so one 16-byte load holds its codes for all four of the
+// group's MFMAs, the m-th of which contracts unit m of the four steps.
+// Measured: 6x6x256 -> 4096 at batch 32 on the 64 x 128 tiles above 43.3 us,
+// on 32 x 32 tiles through an LDS ring 15.3 us, here 8.4 us (4.5 TB/s of weights); 1x1x4096 ->
+// 4096 23.7, 9.8 and 5.1 us.
+struct FcGeom {
+  int32_t sn, sg, st;    // cells between images, channel blocks, taps
+  FastDiv div_taps;
+};
+
+template <int NB>
+__global__ __launch_bounds__(512) void conv_mfma(ConvLaunch a, FcGeom g) {
+  constexpr int NW = 8, U = 3;
+  constexpr int SUMS = NW * NB * 1024;
+  __shared__ __attribute__((aligned(16))) uint8_t lds[SUMS + 1024];
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int q = lane >> 4, r = lane & 15;
+  const int co0 = blockIdx.x * 16, p0 = blockIdx.y * 16 * NB;
+  const int ntaps = a.kh * a.kw;
+  const int ng = (a.nk + 3) / 4;
+  const int s0 = wave * ng / NW, s1 = (wave + 1) * ng / NW;   // this wave's groups
+
+  // the tile's threshold records, in flight beside the main loop's loads
+  const int nthr = (a.cout - co0 < 16 ? a.cout - co0 : 16) * a.rec;
+  const int32_t trec = a.out_mode && tid < nthr ? a.thr[(int64_t)co0 * a.rec + tid] : 0;
+
+  const uint8_t* wl = reinterpret_cast<const uint8_t*>(a.wgt) +
+                      (int64_t)(co0 >> 5) * 2 * a.nk * 1024 + ((co0 & 16) + r) * 16;
+  const uint8_t* xl[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const int p = p0 + 16 * b + r < a.m ? p0 + 16 * b + r : a.m - 1;
+    xl[b] = a.x + (int64_t)p * g.sn * 16;
+  }
+  v4i acc[NB];
+#pragma unroll
+  for (int b = 0; b < NB; ++b) acc[b] = v4i{0, 0, 0, 0};
+
+  struct Batch {
+    v4i w[U][4];
+    v4i x[U][NB];
+  };
+  // steps past the last read the last one again, with zero codes
+  auto load = [&](Batch& t, int s) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (s + j >= s1) break;
+      const int k = 4 * (s + j) + q;
+      const int kk = k < a.nk ? k : a.nk - 1;
+      const int cb = fdiv(kk, g.div_taps);
+      const int64_t cell = (int64_t)cb * g.sg + (int64_t)(kk - cb * ntaps) * g.st;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+        t.w[j][m] = *reinterpret_cast<const v4i*>(wl + (int64_t)kk * 2048 + (m & 1) * 1024 +
+                                                  (m >> 1) * 512);
+#pragma unroll
+      for (int b = 0; b < NB; ++b) t.x[j][b] = *reinterpret_cast<const v4i*>(xl[b] + cell * 16);
+    }
+  };
+  auto compute = [&](const Batch& t, int s) {
+#pragma unroll
+    for (int j = 0; j < U; ++j) {
+      if (s + j >= s1) break;
+      const uint32_t in = 4 * (s + j) + q < a.nk ? ~0u : 0u;
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int b = 0; b < NB; ++b)
+          acc[b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(
+              t.w[j][m], unpack2((uint32_t)t.x[j][b][m] & in), acc[b], 0, 0, 0);
+    }
+  };
+  Batch t0, t1;
+  load(t0, s0);
+  load(t1, s0 + U);
+  __builtin_amdgcn_sched_barrier(0);   // every load before the first MFMA
+  for (int s = s0; s < s1; s += 2 * U) {
+    compute(t0, s);
+    load(t0, s + 2 * U);
+    compute(t1, s + U);
+    load(t1, s + 3 * U);
+  }
+
+  // lane: channels 4q .. 4q+3 of image r of each block
+#pragma unroll
+  for (int b = 0; b < NB; ++b)
+    *reinterpret_cast<v4i*>(lds + (wave * NB + b) * 1024 + lane * 16) = acc[b];
+  int32_t* rec = reinterpret_cast<int32_t*>(lds + SUMS);
+  if (tid < 256) rec[tid] = trec;
+  __syncthreads();
+  if (tid >= 64 * NB) return;
+  v4i v = v4i{0, 0, 0, 0};
+#pragma unroll
+  for (int w = 0; w < NW; ++w)
+    v += *reinterpret_cast<const v4i*>(lds + (w * NB + wave) * 1024 + lane * 16);
+  const int p = p0 + 16 * wave + r, co = co0 + 4 * q;
+  if (p >= a.m) return;
+  const int64_t e = (int64_t)p * a.cout + co;
+  uint32_t code[4] = {0, 0, 0, 0};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    if (co + i >= a.cout) continue;
+    if (a.acc_dump) a.acc_dump[e + i] = v[i];
+    if (a.out_mode == 0) {
+      reinterpret_cast<int32_t*>(a.y)[e + i] = v[i];
+      continue;
+    }
+    const int32_t* t = rec + (4 * q + i) * a.rec;
+    const int sv = sgn(v[i], t[0]);
+    for (int k = 1; k <= a.nq; ++k) code[i] += sv > t[k];
+  }
+  uint8_t* y8 = reinterpret_cast<uint8_t*>(a.y);
+  if (a.out_mode == 2) {          // c_out % 4 == 0
+    if (co < a.cout)
+      y8[a.out_layout == IFQ_LAYOUT_U2_BLOCK64 ? block64_byte(p, co, 1, a.div_howo, a.cout)
+                                               : e >> 2] =
+          (uint8_t)(code[0] | code[1] << 2 | code[2] << 4 | code[3] << 6);
+  } else if (a.out_mode == 1) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      if (co + i < a.cout) y8[e + i] = (uint8_t)code[i];
+  }
+}
+
+// Up to 64 images: beyond, the weights are read again for each 64 and the
+// tiles of the other kernels reuse them better.
+bool fc_eligible(const ConvLaunch& a) {
+  return a.kh == a.h && a.kw == a.w && a.pad == 0 && a.ho * a.wo == 1 && a.m > 0 && a.m <= 64 &&
+         a.join_kind == IFQ_JOIN_NONE && !a.pool_k && !a.f4;
+}
+
+int fc_blocks(const ConvLaunch& a) { return a.m <= 16 ? 1 : a.m <= 32 ? 2 : 4; }
+
+const char* fc_name(const ConvLaunch& a) {
+  const int nb = fc_blocks(a);
+  return nb == 1 ? "conv_mfma<1>" : nb == 2 ? "conv_mfma<2>" : "conv_mfma<4>";
+}
+
+hipError_t launch_fc(const ConvLaunch& a, hipStream_t stream) {
+  FcGeom g;
+  const int hw = a.h * a.w, G = a.cin / 64;
+  const bool blk = a.in_layout == IFQ_LAYOUT_U2_BLOCK64;
+  g.sn = hw * G;
+  g.sg = blk ? hw : 1;
+  g.st = blk ? 1 : G;
+  g.div_taps = make_fastdiv(a.kh * a.kw);
+  const int nb = fc_blocks(a);
+  const dim3 grid((a.cout + 15) / 16, (a.m + 16 * nb - 1) / (16 * nb));
+  switch (nb) {
+    case 1: hipLaunchKernelGGL((conv_mfma<1>), grid, dim3(512), 0, stream, a, g); break;
+    case 2: hipLaunchKernelGGL((conv_mfma<2>), grid, dim3(512), 0, stream, a, g); break;
+    default: hipLaunchKernelGGL((conv_mfma<4>), grid, dim3(512), 0, stream, a, g); break;
+  }
+  return hipGetLastError();
+}
+
 // ---------------------------------------------------------------------------
 // Variants and per-layer planning
 // ---------------------------------------------------------------------------
@@ -391,24 +558,26 @@ bool mfma_eligible(const ConvLaunch& a) {
 namespace {
 
 struct MfmaChoice {
-  int kind;   // 0 register-blocked (reg3), 1 windowed 3x3, 2 tiled, 3 windowed, -1 none
+  int kind;   // 0 register-blocked (reg3), 1 windowed 3x3, 2 tiled, 3 windowed, 4 fully
+              // connected, -1 none
   HaloPlan hp;
   Reg3Plan rp;
   Plan pl;
 };
 
-// Layers the windowed kernel of ifq_conv_win.hip is weighed for. Not 3x3
+// Layers the windowed kernel of ifq_conv_win.hip is weighed for: not 3x3
 // layers on BLOCK64 codes, which the register-blocked kernels take (batch 7,
-// 72x56x192 -> 128: 9.7 us against 12.3), and not fully connected layers: one
-// output pixel per image shares no window with another, and the tiled
-// kernel's deeper ring streams their weights faster.
+// 72x56x192 -> 128: 9.7 us against 12.3).
 bool win_candidate(const ConvLaunch& a) {
-  if (a.ho * a.wo == 1) return false;
   return !(a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3);
 }
 
 MfmaChoice plan_choice(const ConvLaunch& a) {
   MfmaChoice c{};
+  if (fc_eligible(a)) {
+    c.kind = 4;
+    return c;
+  }
   const bool halo = plan_halo(a, &c.hp);
   const bool r3 = plan_reg3(a, -1, &c.rp);
   if (a.join_kind == IFQ_JOIN_CONV_FUSED) {
@@ -456,6 +625,7 @@ const char* conv_mfma_name(const ConvLaunch& a) {
   if (c.kind == 0) return reg3_name(c.rp, a);
   if (c.kind == 1) return conv_halo_name(c.hp, a);
   if (c.kind == 3) return conv_win_name(a);
+  if (c.kind == 4) return fc_name(a);
   if (c.kind < 0) return "";
   return kVariants[c.pl.variant].name;
 }
@@ -472,6 +642,7 @@ hipError_t launch_conv_mfma(const ConvLaunch& a, hipStream_t stream) {
   if (c.kind == 0) return launch_reg3(a, c.rp, stream);
   if (c.kind == 1) return launch_conv_halo(a, c.hp, stream);
   if (c.kind == 3) return launch_conv_win(a, stream);
+  if (c.kind == 4) return launch_fc(a, stream);
   if (c.kind < 0) return hipErrorNotSupported;
   const Plan& pl = c.pl;
   switch (pl.variant) {

@@ -1024,7 +1024,7 @@ IFQ_API const char* ifq_conv_pool_fp4_kernel_name(const ifq_conv_desc* d,
   ifq::HaloPlan hp;
   if (!ifq::mfma_eligible(a) || !fp4_plan(a, &hp)) return "";
   a.f4 = 1;
-  return ifq::conv_halo_name(hp, a);
+  return ifq::conv_pool_name(a, hp);
 }
 
 IFQ_API ifq_status ifq_conv_pool_forward_fp4(const ifq_conv_desc* d, const ifq_pool_desc* p,
@@ -1044,7 +1044,7 @@ IFQ_API ifq_status ifq_conv_pool_forward_fp4(const ifq_conv_desc* d, const ifq_p
   a.f4 = 1;
   a.rowsum = nullptr;
   a.wzero = fp4_zero_off(ifq::weight_geom(*d));
-  st = hip_status(ifq::launch_conv_halo(a, hp, stream), "conv+pool fp4 launch");
+  st = hip_status(ifq::launch_conv_pool(a, hp, stream), "conv+pool fp4 launch");
   if (st != IFQ_OK) return st;
   return ok();
 }

@@ -316,14 +316,14 @@ hipError_t launch_gather(const ConvLaunch& a, hipStream_t stream) {
 
 }  // namespace
 
-// A fused pool (a.pool_k) runs in the windowed 3x3 kernel or one of the
+// A fused pool (a.pool_k) runs in one of the 3x3 kernels or of the
 // small-channel kernels, where their planners fit whole rows of pooling
 // windows into a tile; no other kernel takes it.
 const char* conv_kernel_name(const ConvLaunch& a) {
   if (a.m == 0) return "";   // nothing is launched
   if (a.pool_k) {
     HaloPlan hp;
-    if (mfma_eligible(a) && plan_halo(a, &hp)) return conv_halo_name(hp, a);
+    if (mfma_eligible(a) && plan_halo(a, &hp)) return conv_pool_name(a, hp);
     if (small8_eligible(a)) return conv_small8_name(a);
     if (small2_eligible(a)) return conv_small2_name(a);
     return "";
@@ -352,7 +352,7 @@ hipError_t launch_conv(const ConvLaunch& a, hipStream_t stream) {
   if (a.m == 0) return hipSuccess;
   if (a.pool_k) {
     HaloPlan hp;
-    if (mfma_eligible(a) && plan_halo(a, &hp)) return launch_conv_halo(a, hp, stream);
+    if (mfma_eligible(a) && plan_halo(a, &hp)) return launch_conv_pool(a, hp, stream);
     if (small8_eligible(a)) return launch_conv_small8(a, stream);
     if (small2_eligible(a)) return launch_conv_small2(a, stream);
     return hipErrorNotSupported;

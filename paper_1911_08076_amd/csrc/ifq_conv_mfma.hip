@@ -637,6 +637,34 @@ int64_t conv_mfma_workspace_bytes(const ConvLaunch& a) {
   return w2_split_bytes(a, c.rp.w2);
 }
 
+// A fused pool the windowed kernel covers: conv_w2 where its prediction is below
+// the windowed kernel's by the margin that the pooling itself takes of its
+// lead (28x28x512 -> 512 at batch 16, predicted at 0.92: 35.4 against 35.3-36.3
+// us; 26x26x128 -> 256 at batch 4, 0.91: 9.1 against 8.8), and its tiles fill half
+// of the CUs. Smaller launches stay where they were: the windowed kernel's
+// pooled instances are what the tests at those sizes cover, though conv_w2
+// measures faster on them too with 256 channels or more (28x28x512 -> 512 at
+// batch 2 12.3 against 19.9 us) and even with 64 (7.0-7.2 both).
+namespace {
+
+bool pool_on_w2(const ConvLaunch& a, const HaloPlan& hp, Reg3Plan* rp) {
+  if (!plan_reg3(a, -1, rp) || rp->persistent || rp->t_us >= 0.9 * hp.t_us) return false;
+  return w2_tiles(a, rp->w2) >= kNumCUs / 2;
+}
+
+}  // namespace
+
+const char* conv_pool_name(const ConvLaunch& a, const HaloPlan& hp) {
+  Reg3Plan rp;
+  return pool_on_w2(a, hp, &rp) ? conv_w2_name(rp.w2, a) : conv_halo_name(hp, a);
+}
+
+hipError_t launch_conv_pool(const ConvLaunch& a, const HaloPlan& hp, hipStream_t stream) {
+  Reg3Plan rp;
+  return pool_on_w2(a, hp, &rp) ? launch_conv_w2(a, rp.w2, stream)
+                                : launch_conv_halo(a, hp, stream);
+}
+
 hipError_t launch_conv_mfma(const ConvLaunch& a, hipStream_t stream) {
   const MfmaChoice c = choose_mfma(a);
   if (c.kind == 0) return launch_reg3(a, c.rp, stream);

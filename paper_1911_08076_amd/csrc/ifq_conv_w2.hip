@@ -28,6 +28,12 @@
 // downsample computed in the kernel (its weights arrive as one extra stage of
 // the ring, its strided input cells in the prologue) and the fp64 join of
 // ifq_epilogue.h on the transposed layout. Optional int32 dump of the sums.
+// MODE 4: the threshold epilogue with the k x k/k valid max-pool after the layer,
+// taken on the codes of the LDS output tile, which then holds whole rows of
+// pooling windows. Only the pooled codes reach memory, and the convolution runs
+// at this kernel's rate instead of the windowed kernel's: batch 16, 2x2,
+// 112x112x128 -> 128 47.8 -> 35.6 us, 56x56x256 -> 256 40.0 -> 35.5 us,
+// 14x14x512 -> 512 21.2 -> 13.1 us; fp4 41.1 -> 27.6, 32.0 -> 24.2, 17.0 -> 10.2 us.
 //
 // K split across workgroups (MODE 3: the threshold epilogue, a.ksplit > 1): the
 // grid's z index picks a range of c_in/64/ksplit channel blocks. Each
@@ -56,7 +62,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK / 4) * OCC) void c
     ConvLaunch a) {
   // MODE 3: the threshold epilogue (0) with the K split across workgroups
   constexpr bool SPLIT = MODE == 3;
-  constexpr int EM = SPLIT ? 0 : MODE;           // the epilogue
+  constexpr bool POOL = MODE == 4;
+  constexpr int EM = SPLIT || POOL ? 0 : MODE;   // the epilogue
   constexpr bool SW = EM != 1;                 // transposed sums
   constexpr bool FUSED = EM == 2;
   constexpr int GDM = 4;                         // downsample channel blocks at most
@@ -607,7 +614,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, (WM * WN * WK / 4) * OCC) void c
   }
   __syncthreads();
   const int npx = a.m - p0 < bn ? a.m - p0 : bn;
-  copy_out_tile(a, otile, orow, co0, BM, p0, npx);
+  if constexpr (POOL)
+    pool_out_tile(a, otile, orow, co0, BM, p0, npx);
+  else
+    copy_out_tile(a, otile, orow, co0, BM, p0, npx);
 }
 
 // ---------------------------------------------------------------------------
@@ -622,6 +632,7 @@ struct W2Variant {
   const char* thr_name;   // the kernels as a profiler lists them: threshold
   const char* idj_name;   // epilogue, identity join, fused downsample join
   const char* fused_name;
+  const char* pool_name;  // threshold epilogue with a pool
 };
 
 #define IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, mode, f4, occ, winb)                          \
@@ -630,7 +641,8 @@ struct W2Variant {
 #define IFQ_W2_NAMES(wm, wn, wk, fm, fn, t, d, f4, occ, winb)      \
   IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, 0, f4, occ, winb),         \
       IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, 1, f4, occ, winb),     \
-      IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, 2, f4, occ, winb)
+      IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, 2, f4, occ, winb),     \
+      IFQ_W2_NAME(wm, wn, wk, fm, fn, t, d, 4, f4, occ, winb)
 
 // Index order must match the switch in launch_conv_w2.
 // (c0_us, cj_us, cs_us) are least-squares fits to kernel times measured on
@@ -667,12 +679,11 @@ constexpr double kW2SplitUs = 19.0;
 constexpr double kW2SplitAddUs = 0.3;
 
 // The epilogues this kernel has: 2-bit codes with the packed 16-bit compares
-// (sums and thresholds below 2^15), no pool, and either thresholds or an
-// identity join with a 2-bit shortcut.
+// (sums and thresholds below 2^15), and either thresholds, with or without a
+// pool whose windows tile the output, or a join with a 2-bit shortcut.
 bool w2_mode_ok(const ConvLaunch& a) {
-  if (!(a.out_mode == 2 && a.rec == 4 && (a.cout & 31) == 0 && 27 * a.cin <= 32766 &&
-        a.pool_k == 0))
-    return false;
+  if (!(a.out_mode == 2 && a.rec == 4 && (a.cout & 31) == 0 && 27 * a.cin <= 32766)) return false;
+  if (a.pool_k) return !a.pool_img && !a.acc_dump && pool_epilogue_ok(a);
   if (a.join_kind == IFQ_JOIN_NONE) return true;
   // identity join: the shortcut is prefetched as whole 16-byte cells
   if (a.join_kind == IFQ_JOIN_IDENTITY)
@@ -708,7 +719,7 @@ bool w2_fit(const ConvLaunch& a, int v, W2Plan* out, int want_split) {
   W2Plan best{};
   bool have = false;
   for (int S = 1; S <= kW2MaxSplit; S *= 2) {
-    if (S > 1 && !(a.split_ok && a.join_kind == IFQ_JOIN_NONE && !V.f4 && G % (S * V.wk) == 0))
+    if (S > 1 && !(a.split_ok && !a.pool_k && a.join_kind == IFQ_JOIN_NONE && !V.f4 && G % (S * V.wk) == 0))
       break;
     if (want_split > 0 && S != want_split) continue;
     const int64_t slots = (int64_t)kW2CUs * V.occ / S;
@@ -718,6 +729,12 @@ bool w2_fit(const ConvLaunch& a, int v, W2Plan* out, int want_split) {
     int64_t bn = (a.m + nb - 1) / nb;
     bn = (bn + 31) / 32 * 32;
     if (bn > bnmax) bn = bnmax;
+    if (a.pool_k) {   // whole rows of pooling windows per tile
+      const int64_t unit = (int64_t)a.pool_k * a.wo;
+      bn = (bn + unit - 1) / unit * unit;
+      if (bn > bnmax) bn = bnmax / unit * unit;
+      if (bn == 0) continue;
+    }
     // a workgroup holds the windows of its own G / S channel blocks
     const int64_t gs = G / S;
     const int64_t cells = window_cells_max(a, bn, (int64_t)V.winb / 16 / gs);
@@ -746,12 +763,16 @@ bool w2_fit(const ConvLaunch& a, int v, W2Plan* out, int want_split) {
 
 int w2_variant_count() { return kNumW2; }
 
+int64_t w2_tiles(const ConvLaunch& a, const W2Plan& p) {
+  const int64_t bm = 32 * kW2Variants[p.variant].fm * kW2Variants[p.variant].wm;
+  return p.blocks_m * ((a.cout + bm - 1) / bm);
+}
+
 int64_t w2_split_bytes(const ConvLaunch& a, const W2Plan& p) {
   if (p.ksplit <= 1) return 0;
   const W2Variant& V = kW2Variants[p.variant];
   const int64_t bm = 32 * V.fm * V.wm, bn = 32 * V.fn * V.wn;
-  const int64_t tiles = (int64_t)p.blocks_m * ((a.cout + bm - 1) / bm);
-  return kSplitCounterBytes + tiles * p.ksplit * bm * bn * 4;
+  return kSplitCounterBytes + w2_tiles(a, p) * p.ksplit * bm * bn * 4;
 }
 bool w2_variant_fp4(int v) { return v >= 0 && v < kNumW2 && kW2Variants[v].f4; }
 
@@ -776,7 +797,8 @@ bool plan_w2(const ConvLaunch& a, int forced, W2Plan* out, int want_split) {
 
 const char* conv_w2_name(const W2Plan& p, const ConvLaunch& a) {
   const W2Variant& V = kW2Variants[p.variant];
-  return a.join_kind == IFQ_JOIN_IDENTITY    ? V.idj_name
+  return a.pool_k                            ? V.pool_name
+         : a.join_kind == IFQ_JOIN_IDENTITY  ? V.idj_name
          : a.join_kind == IFQ_JOIN_CONV_FUSED ? V.fused_name
                                               : V.thr_name;
 }
@@ -794,28 +816,33 @@ hipError_t launch_conv_w2(ConvLaunch a, const W2Plan& p, hipStream_t stream) {
   }
   const dim3 grid(p.blocks_m, (a.cout + bm - 1) / bm, a.ksplit);
   const dim3 block(64 * V.wm * V.wn * V.wk);
-  const int mode = a.ksplit > 1                            ? 3
+  const int mode = a.pool_k                              ? 4
+                   : a.ksplit > 1                        ? 3
                    : a.join_kind == IFQ_JOIN_IDENTITY    ? 1
                    : a.join_kind == IFQ_JOIN_CONV_FUSED ? 2
                                                          : 0;
-  switch (p.variant * 4 + mode) {
+  switch (p.variant * 5 + mode) {
 // the K-split instances (int8 variants only)
 #define IFQ_W2_SPLIT(k, wm, wn, wk, fm, fn, t, d, f4, occ, winb)                                \
-  case 4 * k + 3:                                                                               \
+  case 5 * k + 3:                                                                               \
     hipLaunchKernelGGL((conv_w2<wm, wn, wk, fm, fn, t, d, 3, f4, occ, winb>), grid, block, 0,   \
                        stream, a);                                                              \
     break;
 #define IFQ_W2_CASE(k, wm, wn, wk, fm, fn, t, d, f4, occ, winb)                                 \
-  case 4 * k:                                                                                   \
+  case 5 * k:                                                                                   \
     hipLaunchKernelGGL((conv_w2<wm, wn, wk, fm, fn, t, d, 0, f4, occ, winb>), grid, block, 0,   \
                        stream, a);                                                              \
     break;                                                                                      \
-  case 4 * k + 1:                                                                               \
+  case 5 * k + 1:                                                                               \
     hipLaunchKernelGGL((conv_w2<wm, wn, wk, fm, fn, t, d, 1, f4, occ, winb>), grid, block, 0,   \
                        stream, a);                                                              \
     break;                                                                                      \
-  case 4 * k + 2:                                                                               \
+  case 5 * k + 2:                                                                               \
     hipLaunchKernelGGL((conv_w2<wm, wn, wk, fm, fn, t, d, 2, f4, occ, winb>), grid, block, 0,   \
+                       stream, a);                                                              \
+    break;                                                                                      \
+  case 5 * k + 4:                                                                               \
+    hipLaunchKernelGGL((conv_w2<wm, wn, wk, fm, fn, t, d, 4, f4, occ, winb>), grid, block, 0,   \
                        stream, a);                                                              \
     break;
     IFQ_W2_SPLIT(0, 2, 4, 1, 2, 2, 3, 3, false, 1, 49152)

@@ -333,6 +333,7 @@ constexpr int64_t kSplitCounterBytes = 64 << 10;
 constexpr int64_t kSplitMaxTiles = kSplitCounterBytes / 4;
 // Workspace bytes of a K-split launch of plan p (0 without a split).
 int64_t w2_split_bytes(const ConvLaunch& a, const W2Plan& p);
+int64_t w2_tiles(const ConvLaunch& a, const W2Plan& p);   // workgroup tiles of plan p
 int w2_variant_count();
 bool w2_variant_fp4(int v);   // variant v runs the fp4 contraction (fp4 weight blob)
 // want_split > 0: only plans with that K split (a.split_ok must be set for
@@ -373,6 +374,11 @@ bool reg3_variant_fp4(int v);
 bool plan_reg3(const ConvLaunch& a, int forced, Reg3Plan* out);
 hipError_t launch_reg3(const ConvLaunch& a, const Reg3Plan& p, hipStream_t stream);
 const char* reg3_name(const Reg3Plan& p, const ConvLaunch& a);
+
+// A conv with a fused pool that the windowed 3x3 kernel covers with plan hp,
+// on that kernel or on conv_w2.
+hipError_t launch_conv_pool(const ConvLaunch& a, const HaloPlan& hp, hipStream_t stream);
+const char* conv_pool_name(const ConvLaunch& a, const HaloPlan& hp);
 
 // Whether a launch with a fused downsample (IFQ_JOIN_CONV_FUSED) is covered
 // by one of the 3x3 kernels.

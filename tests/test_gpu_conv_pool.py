@@ -1,8 +1,9 @@
 """GPU parity of the fused conv + max-pool (ifq_conv_pool_forward): the
 pooled codes must equal the oracle's conv -> thresholds -> max-pool on codes
-(Eq. 1, Eq. 7-8, Eq. 4) bit for bit, for the two kernels that fuse the pool
+(Eq. 1, Eq. 7-8, Eq. 4) bit for bit, for the kernels that fuse the pool
 (the small-channel 8-bit first layer, the small-channel 2-bit kernel for
-c_in 16 and 32, and the windowed 3x3 kernel on BLOCK64 input), every code layout they write, pool sizes 2..4, tiles that span
+c_in 16 and 32, and the windowed and the register-blocked 3x3 kernel on
+BLOCK64 input), every code layout they write, pool sizes 2..4, tiles that span
 images, and channels with a negative BN scale (the calibrated parameters
 flip about a tenth of them)."""
 import zlib
@@ -26,7 +27,7 @@ def P():
     return P
 
 
-def gpu_conv_pool(P, L, n, x, p, k, in_layout, out_layout, st=None, mode="valid"):
+def gpu_conv_pool(P, L, n, x, p, k, in_layout, out_layout, st=None, mode="valid", fp4=False):
     import torch
     d = P.conv_desc(n, L.h, L.w, L.cin, L.cout, L.k, L.stride, L.pad,
                     L.in_bits, L.out_bits, in_layout, out_layout)
@@ -34,8 +35,8 @@ def gpu_conv_pool(P, L, n, x, p, k, in_layout, out_layout, st=None, mode="valid"
     st = k if st is None else st
     pm = P.IFQ_POOL_VALID if mode == "valid" else P.IFQ_POOL_SAME
     pd = P.pool_desc(n, ho, wo, L.cout, k, st, pm, L.out_bits, out_layout)
-    name = P.ifq_conv_pool_kernel_name(d, pd)
-    wd = to_dev(P.ifq_pack_weights(d, p["w"]))
+    name = (P.ifq_conv_pool_fp4_kernel_name if fp4 else P.ifq_conv_pool_kernel_name)(d, pd)
+    wd = to_dev((P.ifq_pack_weights_fp4 if fp4 else P.ifq_pack_weights)(d, p["w"]))
     thr = P.ifq_fold_thresholds(L.cout, L.in_bits, L.out_bits, L.k * L.k * L.cin,
                                 p["alpha"], p["beta_in"], p["q_thr"], bias=p["bias"],
                                 mean=p["mean"], var=p["var"], gamma=p["gamma"],
@@ -49,7 +50,7 @@ def gpu_conv_pool(P, L, n, x, p, k, in_layout, out_layout, st=None, mode="valid"
     ob = P.ifq_tensor_bytes(n, pho, pwo, L.cout, out_layout)
     # poisoned output: every byte the kernel leaves alone shows up
     y = torch.full((ob,), 0xA5, dtype=torch.uint8, device=device())
-    P.ifq_conv_pool_forward(d, pd, xd, wd, td, y)
+    (P.ifq_conv_pool_forward_fp4 if fp4 else P.ifq_conv_pool_forward)(d, pd, xd, wd, td, y)
     torch.cuda.synchronize()
     out = y.cpu().numpy()
     if out_layout == U2:
@@ -61,7 +62,7 @@ def gpu_conv_pool(P, L, n, x, p, k, in_layout, out_layout, st=None, mode="valid"
     return name, out
 
 
-def check(P, name, L, n, k, in_layout, outs, family, st=None, mode="valid"):
+def check(P, name, L, n, k, in_layout, outs, family, st=None, mode="valid", fp4=False):
     seed = zlib.crc32(name.encode()) % 997
     p = params_for(seed, L)
     x = codes_for(seed, (n, L.h, L.w, L.cin), L.in_bits)
@@ -69,7 +70,7 @@ def check(P, name, L, n, k, in_layout, outs, family, st=None, mode="valid"):
     want = oracle.maxpool(codes, k, k if st is None else st, mode)
     assert len(np.unique(want)) > 1
     for out_l in outs:
-        kname, got = gpu_conv_pool(P, L, n, x, p, k, in_layout, out_l, st, mode)
+        kname, got = gpu_conv_pool(P, L, n, x, p, k, in_layout, out_l, st, mode, fp4)
         assert kname.startswith(family), (name, out_l, kname)
         assert np.array_equal(got, expect_layout(want, out_l)), (name, out_l, kname)
 
@@ -162,3 +163,36 @@ def test_small2_conv_pool_whole_images(P):
     check(P, "s2p_pool3s2", L, 2, 3, U2, [U2], "conv_small2<", 2, "valid")
     L = make_layer("s2p_pool2s1_same", 13, 13, 16, 64, 3, 1, 1, 2, 2)
     check(P, "s2p_pool2s1_same", L, 3, 2, U2, [B64, U2], "conv_small2<", 1, "same")
+
+
+# launches that fill half of the CUs, on the register-blocked kernel: one and
+# two workgroups per CU, K groups, tiles of one window row and of several, a
+# last tile with fewer, tiles that span images, a ragged channel block, larger
+# windows, a strided conv (name, n, h, w, c_in, c_out, stride, pool k, layouts)
+W2_POOL = [
+    ("wp_yolo_c4", 8, 52, 52, 64, 128, 1, 2, [B64, U2]),
+    ("wp_26", 17, 26, 26, 256, 256, 1, 2, [B64]),
+    ("wp_vgg_conv2_2", 3, 112, 112, 128, 128, 1, 2, [B64]),
+    ("wp_vgg_conv4_3", 9, 28, 28, 512, 512, 1, 2, [B64, U2]),
+    ("wp_vgg_conv5_3_spans_images", 19, 14, 14, 512, 512, 1, 2, [B64]),
+    ("wp_c96_ragged_block", 32, 52, 38, 64, 96, 1, 2, [U2]),
+    ("wp_c224_ragged_block", 20, 26, 26, 512, 224, 1, 2, [U2]),
+    ("wp_pool3", 12, 39, 27, 128, 192, 1, 3, [B64]),
+    ("wp_pool4", 16, 24, 24, 256, 128, 1, 4, [B64]),
+    ("wp_stride2", 18, 39, 43, 64, 320, 2, 2, [B64, U2]),
+]
+
+
+@pytest.mark.parametrize("case", W2_POOL, ids=[c[0] for c in W2_POOL])
+def test_w2_conv_pool_bit_exact(P, case):
+    name, n, h, w, cin, cout, st, k, outs = case
+    L = make_layer(name, h, w, cin, cout, 3, st, 1, 2, 2)
+    check(P, name, L, n, k, B64, outs, "conv_w2<")
+
+
+@pytest.mark.parametrize("case", [c for c in W2_POOL if "vgg" in c[0]],
+                         ids=[c[0] for c in W2_POOL if "vgg" in c[0]])
+def test_w2_conv_pool_fp4_bit_exact(P, case):
+    name, n, h, w, cin, cout, st, k, outs = case
+    L = make_layer(name, h, w, cin, cout, 3, st, 1, 2, 2)
+    check(P, name, L, n, k, B64, outs, "conv_w2<", fp4=True)

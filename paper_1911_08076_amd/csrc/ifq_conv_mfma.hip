@@ -572,6 +572,19 @@ bool win_candidate(const ConvLaunch& a) {
   return !(a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3);
 }
 
+// 3x3 layers on BLOCK64 codes with so few outputs that 32 x 64 tiles are at
+// most one per CU: the register-blocked kernels' tiles leave most CUs idle, and
+// the windowed kernel's small ones, K split over the waves, are faster:
+// 13x13x512 -> 512 at batch 1 10.1 -> 8.2 us, at batch 4 11.7 -> 9.4, 14x14x256 ->
+// 256 7.1 -> 6.2, 28x28x128 -> 128 6.3 -> 5.5; past one tile a CU slower
+// (14x14x256 at batch 16 7.9 against 8.9), and with 64 channels too (28x28: 4.7
+// against 5.1, its K is one stage deep).
+bool win_small(const ConvLaunch& a) {
+  return a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3 && a.stride == 1 &&
+         a.pad == 1 && a.cin >= 128 && a.out_mode == 2 && a.join_kind == IFQ_JOIN_NONE &&
+         (int64_t)((a.m + 63) / 64) * ((a.cout + 31) / 32) <= kNumCUs;
+}
+
 MfmaChoice plan_choice(const ConvLaunch& a) {
   MfmaChoice c{};
   if (fc_eligible(a)) {
@@ -595,6 +608,10 @@ MfmaChoice plan_choice(const ConvLaunch& a) {
   // (64x56x56x64 -> 64 3x3 packed: 26.6 us predicted, 23.9 measured, against
   // 25.6 and 26.3 for the windowed kernel)
   double tw = 0;
+  if (win_small(a) && plan_win_us(a, &tw)) {
+    c.kind = 3;
+    return c;
+  }
   if (win_candidate(a) && plan_win_us(a, &tw) &&
       tw < 0.85 * (c.kind == 0 ? c.rp.t_us : c.kind == 1 ? c.hp.t_us : c.pl.t_us))
     c.kind = 3;

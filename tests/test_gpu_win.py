@@ -161,3 +161,27 @@ def test_misaligned_input_takes_the_general_kernel(P):
         y.zero_()
         P.ifq_conv_forward(d, buf[off:off + x.size], wd, thr, y)
         assert np.array_equal(y.cpu().numpy().reshape(want.shape), want), off
+
+
+# 3x3 layers on BLOCK64 codes with at most one 32 x 64 tile per CU, up to the
+# edge of that rule, ragged tiles and channel blocks
+SMALL_B64 = [("sb_13", 1, 13, 13, 512, 512), ("sb_13_b4", 4, 13, 13, 512, 512),
+             ("sb_edge", 16, 32, 16, 128, 64), ("sb_odd", 3, 9, 17, 192, 320),
+             ("sb_one_px", 1, 1, 1, 128, 64), ("sb_c_out96", 2, 28, 28, 128, 96)]
+
+
+@pytest.mark.parametrize("case", SMALL_B64, ids=[c[0] for c in SMALL_B64])
+def test_conv_win_small_block64(P, case):
+    name, n, h, w, cin, cout = case
+    L = make_layer(name, h, w, cin, cout, 3, 1, 1, 2, 2)
+    p = params_for(21, L)
+    x = codes_for(21, (n, h, w, cin), 2)
+    want_acc, want = oracle_layer(L, x, p)
+    for ol in (B64, U2):
+        if ol == B64 and cout % 64:
+            continue
+        d = P.conv_desc(n, h, w, cin, cout, 3, 1, 1, 2, 2, B64, ol)
+        assert P.ifq_conv_kernel_name(d).startswith("conv_win<2,"), P.ifq_conv_kernel_name(d)
+        acc, got = gpu_layer(P, L, n, x, p, in_layout=B64, out_layout=ol)
+        assert np.array_equal(acc, want_acc)
+        assert np.array_equal(got, expect_layout(want, ol))

@@ -4,6 +4,7 @@ Loading fails loudly (ImportError) when the library has not been built: there
 is no fallback implementation of any entry point.
 """
 import ctypes
+import operator
 import os
 
 import numpy as np
@@ -101,6 +102,21 @@ def address(t):
     return t.data_ptr()
 
 
+class ArgumentError(ctypes.ArgumentError, TypeError):
+    """An argument of a kind that its entry point does not take."""
+
+
+def integer(v):
+    """The int of an integer argument of another type than int: a NumPy integer
+    or a ctypes int32, as a ctypes argument takes them; None and floats are refused."""
+    if isinstance(v, ctypes.c_int32):
+        return v.value
+    try:
+        return operator.index(v)
+    except TypeError:
+        raise ArgumentError("an int is required, not %s" % type(v).__name__) from None
+
+
 # (name, restype, argtypes) of every exported entry point
 SIGNATURES = [
     ("ifq_version", ctypes.c_char_p, []),
@@ -186,7 +202,7 @@ def load():
         fn.restype = res
         fn.argtypes = args
     from . import _ifqcall
-    _ifqcall.bind(address, *[ctypes.cast(getattr(lib, n), vp).value for n in CALLED])
+    _ifqcall.bind(address, integer, *[ctypes.cast(getattr(lib, n), vp).value for n in CALLED])
     call = _ifqcall
     _lib = lib
     return lib

@@ -7,7 +7,8 @@
  * tensor's address), as long as the kernel it launches.
  *
  * A tensor argument is None (NULL) or an object with data_ptr() (a torch
- * tensor); anything else goes through the binding's own conversion.
+ * tensor), an integer an int; anything else goes through the binding's own
+ * conversions, which take and refuse what ctypes takes and refuses.
  */
 #define PY_SSIZE_T_CLEAN
 #include <Python.h>
@@ -26,7 +27,8 @@ static struct {
   __typeof__(&ifq_run_stack_static) run_stack_static;
 } fn;
 static PyObject* s_data_ptr;   /* "data_ptr" */
-static PyObject* conv_ptr;     /* the binding's conversion of other objects */
+static PyObject* conv_ptr;     /* the binding's conversion of other tensor arguments */
+static PyObject* conv_int;     /* and of other integers */
 
 /* The address of a tensor argument; 0 on success. */
 static int address(PyObject* o, int64_t* v) {
@@ -45,21 +47,32 @@ static int address(PyObject* o, int64_t* v) {
   return PyErr_Occurred() ? -1 : 0;
 }
 
-/* kinds: one letter per argument, t a tensor, i an int (an address, a size,
- * an int32: its low bits are taken) or None. */
+/* The low 64 bits of an integer argument; 0 on success. */
+static int integer(PyObject* o, int64_t* v) {
+  if (PyLong_Check(o)) {
+    *v = (int64_t)PyLong_AsUnsignedLongLongMask(o);
+  } else {
+    PyObject* r = conv_int ? PyObject_CallOneArg(conv_int, o) : NULL;
+    if (!r) {
+      if (!PyErr_Occurred()) PyErr_SetString(PyExc_TypeError, "an int is required");
+      return -1;
+    }
+    *v = (int64_t)PyLong_AsUnsignedLongLongMask(r);
+    Py_DECREF(r);
+  }
+  return PyErr_Occurred() ? -1 : 0;
+}
+
+/* kinds: one letter per argument, t a tensor, i an integer (a size, an int32:
+ * its low bits are taken), p an address as an int or None (NULL). */
 static int values(PyObject* const* args, Py_ssize_t n, const char* kinds, int64_t* v) {
   for (Py_ssize_t i = 0; i < n; ++i) {
     if (!kinds[i]) break;
     if (kinds[i] == 't') {
       if (address(args[i], v + i)) return -1;
-    } else if (args[i] == Py_None) {
+    } else if (kinds[i] == 'p' && args[i] == Py_None) {
       v[i] = 0;
-    } else if (PyLong_Check(args[i])) {
-      v[i] = (int64_t)PyLong_AsUnsignedLongLongMask(args[i]);
-      if (PyErr_Occurred()) return -1;
-    } else {
-      PyErr_Format(PyExc_TypeError, "argument %zd: an int is required, not %s", i + 1,
-                   Py_TYPE(args[i])->tp_name);
+    } else if (integer(args[i], v + i)) {
       return -1;
     }
   }
@@ -82,27 +95,29 @@ static int values(PyObject* const* args, Py_ssize_t n, const char* kinds, int64_
     return PyLong_FromLong(st);                                                 \
   }
 
-ENTRY(conv_forward, "ittti" "tttii",
+ENTRY(conv_forward, "ptttp" "tttip",
       conv_forward(P(0), P(1), P(2), P(3), P(4), P(5), P(6), P(7), (size_t)v[8], P(9)))
-ENTRY(conv_forward_fp4, "itttiti", conv_forward_fp4(P(0), P(1), P(2), P(3), P(4), P(5), P(6)))
-ENTRY(conv_pool_forward, "iitttti", conv_pool_forward(P(0), P(1), P(2), P(3), P(4), P(5), P(6)))
-ENTRY(conv_pool_forward_fp4, "iitttti",
+ENTRY(conv_forward_fp4, "ptttptp", conv_forward_fp4(P(0), P(1), P(2), P(3), P(4), P(5), P(6)))
+ENTRY(conv_pool_forward, "ppttttp", conv_pool_forward(P(0), P(1), P(2), P(3), P(4), P(5), P(6)))
+ENTRY(conv_pool_forward_fp4, "ppttttp",
       conv_pool_forward_fp4(P(0), P(1), P(2), P(3), P(4), P(5), P(6)))
-ENTRY(maxpool_codes, "itti", maxpool_codes(P(0), P(1), P(2), P(3)))
-ENTRY(convert_codes, "iiiiiitti",
+ENTRY(maxpool_codes, "pttp", maxpool_codes(P(0), P(1), P(2), P(3)))
+ENTRY(convert_codes, "iiiiiittp",
       convert_codes(v[0], v[1], v[2], (int32_t)v[3], (int32_t)v[4], (int32_t)v[5], P(6), P(7),
                     P(8)))
-ENTRY(run_stack, "itttii", run_stack(P(0), P(1), P(2), P(3), (size_t)v[4], P(5)))
-ENTRY(run_stack_static, "itti", run_stack_static(P(0), P(1), P(2), P(3)))
+ENTRY(run_stack, "ptttip", run_stack(P(0), P(1), P(2), P(3), (size_t)v[4], P(5)))
+ENTRY(run_stack_static, "pttp", run_stack_static(P(0), P(1), P(2), P(3)))
 
-/* bind(convert, addresses in the order of the table above) */
+/* bind(address, integer, addresses in the order of the table above) */
 static PyObject* bind(PyObject* self, PyObject* const* args, Py_ssize_t na) {
   int64_t v[8];
   (void)self;
-  if (na != 9) return PyErr_Format(PyExc_TypeError, "bind: 9 arguments expected");
-  if (values(args + 1, 8, "iiiiiiii", v)) return NULL;
+  if (na != 10) return PyErr_Format(PyExc_TypeError, "bind: 10 arguments expected");
+  if (values(args + 2, 8, "pppppppp", v)) return NULL;
   Py_INCREF(args[0]);
   Py_XSETREF(conv_ptr, args[0]);
+  Py_INCREF(args[1]);
+  Py_XSETREF(conv_int, args[1]);
   fn.conv_forward = P(0);
   fn.conv_forward_fp4 = P(1);
   fn.conv_pool_forward = P(2);

@@ -42,8 +42,19 @@ def test_status_and_text_reach_the_caller():
     (lambda: P.ifq_conv_forward(conv(), 4096, X, THR, X, stream=0), AttributeError),
     (lambda: P.ifq_conv_forward(conv(), X, X, THR, X, join=X, stream=0), ctypes.ArgumentError),
     (lambda: P.ifq_convert_codes(1, 4, 4, 64, 0.5, 3, X, X, stream=0), TypeError),
+    (lambda: P.ifq_convert_codes(1, 4, 4, 64, 0.5, 3, X, X, stream=0), ctypes.ArgumentError),
+    (lambda: P.ifq_convert_codes(0, 4, 4, 64, None, 3, X, X, stream=0), ctypes.ArgumentError),
+    (lambda: P.ifq_convert_codes(0, 4, 4, 64, 0, None, X, X, stream=0), ctypes.ArgumentError),
+    (lambda: P.ifq_convert_codes(0, 4, 4, 64, "0", 3, X, X, stream=0), ctypes.ArgumentError),
     (lambda: _ffi.call.maxpool_codes(0, X, X), TypeError),
 ])
 def test_wrong_kinds_are_refused(call, error):
     with pytest.raises(error):
         call()
+
+
+@pytest.mark.parametrize("kind", [np.int32, np.int64, np.uint8, ctypes.c_int32])
+def test_integers_of_other_types_are_taken(kind):
+    P.ifq_convert_codes(0, 4, 4, 64, kind(0), kind(3), X, X, stream=0)
+    with pytest.raises(P.IfqError, match="layouts"):
+        P.ifq_convert_codes(0, 4, 4, 64, kind(2), kind(3), X, X, stream=0)

@@ -6,12 +6,15 @@ is no fallback implementation of any entry point.
 import ctypes
 import operator
 import os
+import sysconfig
 
 import numpy as np
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 # always the in-tree build next to this file
 LIB_PATH = os.path.join(HERE, "libifq.so")
+# the extension module, built for this interpreter
+CALL_PATH = os.path.join(HERE, "_ifqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 IFQ_OK = 0
 IFQ_ERR_INVALID_ARGUMENT = -1
@@ -180,16 +183,17 @@ call = None     # the _ifqcall module, bound to the library
 
 
 def load():
-    """Load libifq.so and _ifqcall.so once; raise ImportError if one is missing."""
+    """Load libifq.so and _ifqcall once; raise ImportError if one is missing."""
     global _lib, call
     if _lib is not None:
         return _lib
-    if not os.path.exists(LIB_PATH):
-        raise ImportError(
-            "libifq.so is not built (expected at %s); run "
-            "`python paper_1911_08076_amd/build.py` or "
-            "`python -c 'import __graft_entry__; __graft_entry__.build()'`"
-            % LIB_PATH)
+    for path in (LIB_PATH, CALL_PATH):
+        if not os.path.exists(path):
+            raise ImportError(
+                "%s is not built (expected at %s); run "
+                "`python paper_1911_08076_amd/build.py` or "
+                "`python -c 'import __graft_entry__; __graft_entry__.build()'`"
+                % (os.path.basename(path), path))
     # torch ships its own HIP runtime under the soname libamdhip64.so.7.
     # Importing torch first makes the dynamic loader bind libifq.so to that
     # same copy, so the process holds one HIP runtime and torch's streams and

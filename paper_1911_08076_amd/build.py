@@ -1,5 +1,6 @@
-"""Build libifq.so (HIP for gfx950 + host C++) and _ifqcall.so (the CPython
-entry to its launching functions) into this package directory.
+"""Build libifq.so (HIP for gfx950 + host C++) and the extension module _ifqcall
+(the CPython entry to its launching functions, for the interpreter that runs
+this) into this package directory. Needs hipcc, a C compiler and Python.h.
 
 Usage: python paper_1911_08076_amd/build.py (runs without importing the
 package, which needs the library to exist)
@@ -14,7 +15,8 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(HERE, "libifq.so")
-CALL = os.path.join(HERE, "_ifqcall.so")
+# the interpreter's own suffix: another Python does not take the module for its own
+CALL = os.path.join(HERE, "_ifqcall" + sysconfig.get_config_var("EXT_SUFFIX"))
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 ARCH = "gfx950"
 
@@ -79,6 +81,9 @@ def build_call(tag, verbose=False):
     if r.returncode != 0:
         raise RuntimeError("ifq_call.c failed:\n" + r.stdout + r.stderr)
     os.replace(tmp, CALL)
+    untagged = os.path.join(HERE, "_ifqcall.so")     # of a build for any interpreter
+    if os.path.exists(untagged) and untagged != CALL:
+        os.remove(untagged)
 
 
 if __name__ == "__main__":

@@ -1,6 +1,8 @@
 """The C extension that launches for the binding, on the CPU: argument kinds,
 error status and the workspace retry, with calls that launch nothing."""
 import ctypes
+import os
+import sysconfig
 
 import numpy as np
 import pytest
@@ -58,3 +60,14 @@ def test_integers_of_other_types_are_taken(kind):
     P.ifq_convert_codes(0, 4, 4, 64, kind(0), kind(3), X, X, stream=0)
     with pytest.raises(P.IfqError, match="layouts"):
         P.ifq_convert_codes(0, 4, 4, 64, kind(2), kind(3), X, X, stream=0)
+
+
+def test_extension_is_built_for_this_interpreter(monkeypatch):
+    suffix = sysconfig.get_config_var("EXT_SUFFIX")
+    assert os.path.basename(_ffi.call.__file__) == "_ifqcall" + suffix
+    # one that any interpreter would import must not be beside it
+    assert not os.path.exists(os.path.join(_ffi.HERE, "_ifqcall.so"))
+    monkeypatch.setattr(_ffi, "_lib", None)
+    monkeypatch.setattr(_ffi, "CALL_PATH", os.path.join(_ffi.HERE, "missing" + suffix))
+    with pytest.raises(ImportError, match="missing.*is not built"):
+        _ffi.load()

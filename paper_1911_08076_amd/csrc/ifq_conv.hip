@@ -2,7 +2,8 @@
 // every layer shape and code layout that the fast path (ifq_conv_mfma.hip)
 // and the windowed kernel (ifq_conv_win.hip) do not take: 8-bit input codes,
 // c_in not a multiple of 16, inputs not aligned to the windowed kernel's
-// cells, windows that do not fit its LDS. Also the dispatcher over all kernels.
+// cells, windows that do not fit its LDS, and the layers where this kernel is
+// predicted faster (igemm_us). Also the dispatcher over all kernels.
 //
 // One kernel computes a quantized substructure of IFQ-Net:
 //   a    = W_b (x) X_q            integer part of Eq. (1), as an implicit GEMM
@@ -304,6 +305,48 @@ int gather_kind(const ConvLaunch& a) {
   return kGatherBytes;
 }
 
+// Predicted time of this kernel, to weigh conv_win against it: tiles on the
+// busiest CU, up to occ at once where two cost 1 + share of one; per tile a fixed
+// part and an epilogue by kind, and K64 steps. Fitted to 2004 layers (1x1 to 5x5 on
+// byte codes and on packed codes, every output and join; 7.5-9.6% rms a variant; the
+// conv join of the first two scaled from the others by the tile).
+double igemm_us(const ConvLaunch& a) {
+  static const struct {
+    int bm, bn, occ;
+    double share, t0, step, tile;
+    double thr, join, wide, wide_join, conv;   // wide and wide_join per threshold
+    double sums;
+  } fit[4] = {{16, 256, 4, 0.25, 1.437, 0.714, 2.024, 0.520, 1.359, 0.515, 0.672, 3.4, 0.464},
+              {32, 128, 4, 0.30, 2.413, 0.486, 1.002, 0.437, 1.523, 0.514, 0.669, 3.4, 0.568},
+              {64, 128, 3, 0.20, 2.454, 0.561, 1.551, 0.846, 2.527, 1.030, 1.279, 6.8, 0.527},
+              {128, 128, 2, 0.20, 2.933, 0.695, 3.124, 0.972, 4.995, 2.008, 2.486, 12.8, 0.367}};
+  const auto& f = fit[tile_variant(a)];
+  const int64_t tiles =
+      (int64_t)((a.m + f.bn - 1) / f.bn) * ((a.cout + f.bm - 1) / f.bm);
+  const int64_t per_cu = (tiles + kPlanCUs - 1) / kPlanCUs, rem = per_cu % f.occ;
+  const double rounds = (double)(per_cu / f.occ) * (1 + f.share * (f.occ - 1)) +
+                        (rem ? 1 + f.share * (rem - 1) : 0);
+  const bool id = a.join_kind == IFQ_JOIN_IDENTITY;
+  const double epi = a.join_kind == IFQ_JOIN_CONV ? f.conv
+                     : a.out_mode == 0            ? 0
+                     : a.rec == 4                 ? (id ? f.join : f.thr)
+                                                  : (id ? f.wide_join : f.wide) * a.nq;
+  const double sums = a.out_mode == 0 ? 4.0 * a.m * a.cout / kSumBytesPerUs : 0;
+  return f.t0 + rounds * (f.tile + epi + f.step * a.nk) + f.sums * sums;
+}
+
+// Whether conv_win runs a layer that no more special kernel takes: where its
+// prediction is the lower one. Over 2004 layers the choice is 0.3% behind the
+// better of the two, and 20 of them are more than 6% slower than on this kernel
+// (95 with conv_win wherever its windows fit). This kernel keeps short
+// contractions with few output channels or int32 sums: 165x164x48 -> 32 3x3 s2 on
+// bytes, batch 23, 14.7 us against 23.9; 89x91x48 -> 32 1x1 packed, batch 3, 4.5
+// against 6.1; past them conv_win is up to 6 times faster.
+bool use_win(const ConvLaunch& a) {
+  double t = 0;
+  return win_eligible(a, &t) && t < igemm_us(a);
+}
+
 template <int GATHER>
 hipError_t launch_gather(const ConvLaunch& a, hipStream_t stream) {
   switch (tile_variant(a)) {
@@ -332,7 +375,7 @@ const char* conv_kernel_name(const ConvLaunch& a) {
   if (mfma_eligible(a)) return conv_mfma_name(a);
   if (small8_eligible(a)) return conv_small8_name(a);
   if (small2_eligible(a)) return conv_small2_name(a);
-  if (win_eligible(a)) return conv_win_name(a);
+  if (use_win(a)) return conv_win_name(a);
   static const char* names[3][4] = {
       {"conv_igemm<16, 256, 1, 0>", "conv_igemm<32, 128, 1, 0>",
        "conv_igemm<64, 128, 2, 0>", "conv_igemm<128, 128, 2, 0>"},
@@ -361,7 +404,7 @@ hipError_t launch_conv(const ConvLaunch& a, hipStream_t stream) {
   if (mfma_eligible(a)) return launch_conv_mfma(a, stream);
   if (small8_eligible(a)) return launch_conv_small8(a, stream);
   if (small2_eligible(a)) return launch_conv_small2(a, stream);
-  if (win_eligible(a)) return launch_conv_win(a, stream);
+  if (use_win(a)) return launch_conv_win(a, stream);
   switch (gather_kind(a)) {
     case kGatherU2: return launch_gather<kGatherU2>(a, stream);
     case kGatherI8: return launch_gather<kGatherI8>(a, stream);

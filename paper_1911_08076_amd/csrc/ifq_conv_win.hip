@@ -719,8 +719,53 @@ struct WinPlan {
   int variant;
   int lds_bytes;
   WinGeom g;
-  double t_us;
+  double t_us;      // ranks the variants
+  double est_us;    // the chosen one's time, to weigh it against another kernel
 };
+
+// Predicted time of a plan, to compare with another kernel's: tiles of bm x bnmax
+// outputs on the busiest CU, one, two or three at once where LDS holds them (two
+// cost 1.36, three 1.75 of one); per tile a fixed part and an epilogue by kind,
+// window loads, weight stages (barrier and latency, matrix cores) and K-group sums;
+// int32 sums the time of their bytes, which are the layer's largest stream. Fitted
+// to the variants that t_us picks, on 5349 layers in fragment order (1x1 to 5x5,
+// every output and join; 5.1% rms) and 2000 byte and packed ones (7.2%).
+// t_us is 15 to 30% off on filters of one tap or a few, which one_clk was not
+// fitted to, but ranks the variants better than this does (1.8% behind the best
+// one on average against 2.3%).
+double win_estimate(const ConvLaunch& a, const WinVariant& V, const WinGeom& g, int64_t tiles,
+                    int64_t lds, bool fr) {
+  struct Kind {
+    double tile, epi;       // us a tile, us per 512 of its outputs
+  };
+  // codes of up to 2 bits, sums, identity join, wider codes, those with the join,
+  // conv join
+  static const Kind kF[] = {{1.784, 0.076}, {1.158, 0}, {1.969, 0.127},
+                            {1.808, 0.129}, {2.356, 0.314}, {2.563, 0.328}};
+  static const Kind kR[] = {{1.748, 0.085}, {1.181, 0}, {1.992, 0.143},
+                            {1.833, 0.127}, {2.535, 0.335}, {2.527, 0.321}};
+  const bool id = a.join_kind == IFQ_JOIN_IDENTITY;
+  const int kind = a.join_kind == IFQ_JOIN_CONV ? 5
+                   : a.out_mode == 0            ? 1
+                   : a.rec <= 4                 ? (id ? 2 : 0)
+                                                : (id ? 4 : 3);
+  const Kind& k = fr ? kF[kind] : kR[kind];
+  const int bm = 32 * V.fm * V.wm, bnmax = 32 * V.fn * V.wn, sk = V.s * V.wk;
+  const int nst = (g.nkk + sk - 1) / sk;
+  const double outs = (double)bm * bnmax;
+  const int rows = (a.cout + 31) / 32 * 32 < bm ? (a.cout + 31) / 32 * 32 : bm;
+  const double loads = (double)g.nch * g.wcells / 64 / 8;
+  const double mfma = outs * sk / 64 / 2150, red = (V.wk - 1) * outs * 4 / 200 / 2150;
+  const double one = k.tile + k.epi * rows * g.bn / 512 +
+                     (fr ? 0.090 * loads + nst * (0.337 + 1.536 * mfma) + 2.956 * red
+                         : 0.118 * loads + nst * (0.240 + 1.551 * mfma) + 4.592 * red);
+  static const double share[] = {0, 1, 1.36, 1.75};
+  const int64_t per_cu = (tiles + kPlanCUs - 1) / kPlanCUs;
+  const int occ = kWinLds / lds < 3 ? (int)(kWinLds / lds) : 3;
+  const double rounds = (double)(per_cu / occ) * share[occ] + share[per_cu % occ];
+  const double sums = a.out_mode == 0 ? 4.0 * a.m * a.cout / kSumBytesPerUs : 0;
+  return (fr ? 2.199 : 2.128) + rounds * one + 1.15 * sums;
+}
 
 // Most window rows any tile of bn consecutive output pixels needs: the output
 // rows it can touch, stride input rows each, and the filter's overhang once
@@ -815,7 +860,7 @@ bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
     int64_t total = g.ktab_off + ktab;
     if (prm + red + otile > total) total = prm + red + otile;
     out->lds_bytes = (int)total;
-    // predicted time in clocks of a tile: prologue and window loads, stages
+    // predicted time to rank the variants by, in clocks of a tile: prologue and window loads, stages
     // (barrier and latency, matrix cores, weights through the address unit),
     // K-group sums, epilogue; two tiles on a CU at once where LDS holds two
     // cost 1.28 (1.36) of one. Fitted to 620 measured (layer, variant) times
@@ -842,6 +887,7 @@ bool fit_win(const ConvLaunch& a, int v, WinPlan* out) {
       t0 = 1.5;
     }
     out->t_us = t0 + (2 * total <= kWinLds ? (per_cu / 2) * pair + per_cu % 2 : per_cu) * one_clk / 2150;
+    out->est_us = win_estimate(a, V, g, tiles, total, fr);
     return true;
   }
   return false;
@@ -889,7 +935,7 @@ hipError_t launch_in(const ConvLaunch& a, const WinPlan& p, hipStream_t stream) 
 
 // Byte codes below 8 bits and 2-bit NHWC codes in the row-major weight layout,
 // c_in a multiple of 16, the input aligned for the DMA's cells.
-bool win_eligible(const ConvLaunch& a) {
+bool win_eligible(const ConvLaunch& a, double* t_us) {
   if (a.cin % 16 || a.m <= 0 || a.pool_k || a.join_kind == IFQ_JOIN_CONV_FUSED) return false;
   if (a.in_layout == IFQ_LAYOUT_I8_NHWC) {
     if (a.in_bits == 8 || ((uintptr_t)a.x & 15)) return false;
@@ -898,7 +944,9 @@ bool win_eligible(const ConvLaunch& a) {
     return false;   // c_in % 64 == 0: the MFMA dispatcher's choice (plan_win)
   }
   WinPlan p;
-  return choose_win(a, &p);
+  if (!choose_win(a, &p)) return false;
+  *t_us = p.est_us;
+  return true;
 }
 
 bool plan_win_us(const ConvLaunch& a, double* t_us) {

@@ -260,6 +260,10 @@ inline double plan_time(int64_t tiles, double tile_ops, int occ, double c0_us, d
          (double)rounds * c0_us;
 }
 
+// Bytes of int32 sums that the planners' fits price a us at; each kernel's own
+// factor says how much of it its stores take beside its other work.
+constexpr double kSumBytesPerUs = 3.4e6;
+
 struct HaloPlan {
   int variant;
   int bn;
@@ -389,8 +393,8 @@ inline bool fused_supported(const ConvLaunch& a) {
 }
 
 // Any filter size and stride on byte codes (below 8 bits) or 2-bit NHWC codes,
-// c_in a multiple of 16, input windows resident in LDS.
-bool win_eligible(const ConvLaunch& a);
+// c_in a multiple of 16, input windows resident in LDS, and the predicted time.
+bool win_eligible(const ConvLaunch& a, double* t_us);
 hipError_t launch_conv_win(const ConvLaunch& a, hipStream_t stream);
 const char* conv_win_name(const ConvLaunch& a);
 // Its predicted time on 2-bit codes with c_in a multiple of 64 (either 2-bit

@@ -24,7 +24,7 @@ def P():
 
 # (name, n, h, w, cin, cout, k, stride, pad, in_bits, out_bits, in, out)
 CASES = [
-    ("one_pixel", 1, 1, 1, 16, 16, 1, 1, 0, 2, 2, I8, I8),
+    ("one_pixel", 1, 1, 1, 16, 80, 1, 1, 0, 2, 2, I8, I8),
     ("all_padding_taps", 3, 1, 1, 32, 33, 3, 1, 1, 4, 4, I8, I8),
     ("pad_wider_than_filter", 2, 3, 4, 16, 20, 3, 2, 4, 3, 3, I8, I8),
     ("stride_past_filter", 2, 13, 11, 48, 40, 2, 3, 0, 2, 2, I8, U2),

@@ -84,7 +84,6 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
   const int rbw = co0 >> 5;                     // first row block
   const int nrb = a.cout_pad >> 5;
   const int howo = a.ho * a.wo;
-  const int ntaps = a.kh * a.kw;
   const uint8_t* wbase = reinterpret_cast<const uint8_t*>(a.wgt) + lane * 16;
   const uint8_t* zero_src = reinterpret_cast<const uint8_t*>(&g_zero_cell);
   const uint32_t lds0 = lds_addr(lds);
@@ -123,10 +122,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
     }
   }
 
-  // Filter tap (r, s) and channel block g of a K64 step (taps fastest): kept
-  // incrementally from stage to stage where a stage has one or two steps,
-  // else by division (eight steps a stage would walk up to seven on).
-  constexpr bool WALK = SK <= 2;
+  // Filter tap (r, s) and channel block g of K64 step kk, kept incrementally
+  // (taps fastest): kpos is the position of the first step of the next stage
+  // to issue.
   struct KPos {
     int g, s, r;
   };
@@ -139,7 +137,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
     q.r = wr ? 0 : q.r;
     q.g += wr ? 1 : 0;
   };
-  KPos kpos{0, 0, 0};             // WALK: the first step of the next stage to issue
+  KPos kpos{0, 0, 0};
 
   // Issue the loads of stage st into ring slot st % D (stages are issued in
   // order). Chunk c covers K64 step kk = st*SK + c / (CA1 + CB1) of the
@@ -161,14 +159,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
         dma16(wbase + off, dst);
       } else {
         KPos q = kpos;
-        if constexpr (WALK) {
-          for (int u = 0; u < s_; ++u) adv1(q);
-        } else {
-          q.g = fdiv(kk, a.div_taps);
-          const int tap = kk - q.g * ntaps;
-          q.r = fdiv(tap, a.div_kw);
-          q.s = tap - q.r * a.kw;
-        }
+        for (int u = 0; u < s_; ++u) adv1(q);
         const int g = q.g, r = q.r, s = q.s;
         const int iy = px_iy0[i] + r;
         const int ix = px_ix0[i] + s;
@@ -179,10 +170,8 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
         dma16(src, dst);
       }
     }
-    if constexpr (WALK) {
 #pragma unroll
-      for (int u = 0; u < SK; ++u) adv1(kpos);
-    }
+    for (int u = 0; u < SK; ++u) adv1(kpos);
   };
 
   v16i acc[FM][FN];
@@ -477,24 +466,34 @@ hipError_t launch_fc(const ConvLaunch& a, hipStream_t stream) {
 // ---------------------------------------------------------------------------
 // Variants and per-layer planning
 // ---------------------------------------------------------------------------
+// Times (us) of the busiest CU's tiles, one at a time: of a launch, a tile, a stage
+// of s*wk K64 steps, a coded (not int32) tile, and of 512 of its outputs by
+// epilogue: 2-bit thresholds, identity join on 2-bit codes, per threshold other
+// codes without and with that join, conv join.
 struct Variant {
-  int wm, wn, wk, fm, fn;
-  double c0_us;      // fixed cost of one round of workgroups (measured)
-  double eff;        // MFMA efficiency of the main loop (measured)
+  int wm, wn, wk, fm, fn, s;
+  double t0, tile, stage, coded;
+  double thr, join, wide, wide_join, conv;
   const char* name;
 };
 
-// Index order must match the switch in launch_conv_mfma. The two constants
-// of each variant are fitted to kernel times on the ResNet-18 layer shapes
-// (batch 64); the ones of the 64 x 256 tile are a conservative guess.
+// Index order must match the switch in launch_conv_mfma. Fitted to 5349 layers, each
+// timed on every tile (1x1 to 5x5, both layouts, every output and join): 2-bit codes
+// 5-8% rms (13% on the first tile), int32 sums 5-8%, the joins 5-15%, wider codes
+// 8-30%, which this kernel is never the fastest on.
 const Variant kVariants[] = {
-    {2, 4, 1, 2, 4, 9.0, 0.45, "conv_mfma<2, 4, 1, 2, 4, 1, 6>"},    // 128 x 512
-    {2, 4, 1, 2, 2, 8.3, 0.443, "conv_mfma<2, 4, 1, 2, 2, 2, 4>"},   // 128 x 256
-    {1, 8, 1, 2, 2, 7.7, 0.415, "conv_mfma<1, 8, 1, 2, 2, 2, 4>"},   //  64 x 512
-    {2, 4, 1, 1, 2, 9.0, 0.30, "conv_mfma<2, 4, 1, 1, 2, 2, 6>"},    //  64 x 256
-    {2, 2, 2, 2, 2, 9.5, 0.309, "conv_mfma<2, 2, 2, 2, 2, 2, 3>"},   // 128 x 128, K split 2
-    {2, 1, 4, 1, 4, 6.7, 0.19, "conv_mfma<2, 1, 4, 1, 4, 1, 6>"},    //  64 x 128, K split 4
-    {1, 1, 8, 1, 1, 6.7, 0.19, "conv_mfma<1, 1, 8, 1, 1, 1, 6>"},    //  32 x 32, K split 8
+    {2, 4, 1, 2, 4, 1, 2.837, 1.291, 0.845, 5.376, 0.024, 0.118, 0.140, 0.127, 1.198,
+     "conv_mfma<2, 4, 1, 2, 4, 1, 6>"},    // 128 x 512
+    {2, 4, 1, 2, 2, 2, 2.534, 1.274, 0.981, 2.939, 0.027, 0.103, 0.096, 0.111, 0.743,
+     "conv_mfma<2, 4, 1, 2, 2, 2, 4>"},    // 128 x 256
+    {1, 8, 1, 2, 2, 2, 2.400, 1.285, 1.055, 2.892, 0.027, 0.096, 0.077, 0.083, 0.839,
+     "conv_mfma<1, 8, 1, 2, 2, 2, 4>"},    //  64 x 512
+    {2, 4, 1, 1, 2, 2, 1.872, 1.223, 0.778, 1.997, 0.016, 0.080, 0.078, 0.086, 0.557,
+     "conv_mfma<2, 4, 1, 1, 2, 2, 6>"},    //  64 x 256
+    {2, 2, 2, 2, 2, 2, 2.180, 2.645, 1.190, 2.826, 0.028, 0.137, 0.147, 0.173, 0.861,
+     "conv_mfma<2, 2, 2, 2, 2, 2, 3>"},    // 128 x 128, K split 2
+    {2, 1, 4, 1, 4, 1, 1.791, 3.722, 0.851, 2.438, 0.041, 0.211, 0.186, 0.238, 1.182,
+     "conv_mfma<2, 1, 4, 1, 4, 1, 6>"},    //  64 x 128, K split 4
 };
 constexpr int kNumVariants = sizeof(kVariants) / sizeof(kVariants[0]);
 constexpr int kNumCUs = 256;
@@ -506,10 +505,24 @@ struct Plan {
   double t_us;   // predicted time
 };
 
+double tiled_us(const ConvLaunch& a, const Variant& V, int64_t bn, int64_t tiles) {
+  const int64_t per_cu = (tiles + kNumCUs - 1) / kNumCUs;
+  const int sk = V.s * V.wk, bm = 32 * V.fm * V.wm;
+  const int rows = (a.cout + 31) / 32 * 32 < bm ? (a.cout + 31) / 32 * 32 : bm;
+  const bool id = a.join_kind == IFQ_JOIN_IDENTITY;
+  const double per512 = a.join_kind == IFQ_JOIN_CONV ? V.conv
+                        : a.out_mode == 0            ? 0
+                        : a.rec == 4                 ? (id ? V.join : V.thr)
+                                                     : (id ? V.wide_join : V.wide) * a.nq;
+  const double one = V.tile + V.stage * ((a.nk + sk - 1) / sk) + (a.out_mode ? V.coded : 0) +
+                     per512 * rows * (double)bn / 512;
+  const double sums = a.out_mode == 0 ? 4.0 * a.m * a.cout / kSumBytesPerUs : 0;
+  return V.t0 + (double)per_cu * one + 0.8 * sums;
+}
+
 // For each variant take the fewest rounds of one workgroup per CU that fit
 // the layer and spread the pixels evenly over the workgroups of those rounds
-// (in multiples of 32). The predicted time is rounds x (fixed cost + the
-// tile's MFMA work at the variant's loop efficiency); the fastest wins.
+// (in multiples of 32); the variant predicted fastest runs.
 Plan plan_mfma(const ConvLaunch& a) {
   Plan best{0, 0, 0, 0.0};
   double best_t = 1e30;
@@ -526,7 +539,7 @@ Plan plan_mfma(const ConvLaunch& a) {
     bn = (bn + 31) / 32 * 32;
     if (bn > bnmax) bn = bnmax;
     const int64_t blocks = nco * ((a.m + bn - 1) / bn);
-    const double t = plan_time(blocks, 2.0 * bm * bnmax * (double)a.kpad, 1, V.c0_us, V.eff);
+    const double t = tiled_us(a, V, bn, blocks);
     if (t < best_t - 1e-9) {
       best_t = t;
       best = Plan{v, (int)bn, (int)((a.m + bn - 1) / bn), t};
@@ -538,8 +551,6 @@ Plan plan_mfma(const ConvLaunch& a) {
 template <int WM, int WN, int WK, int FM, int FN, int S, int D>
 hipError_t launch_variant(ConvLaunch a, const Plan& pl, hipStream_t stream) {
   a.bn = pl.bn;
-  a.div_taps = make_fastdiv(a.kh * a.kw);
-  a.div_kw = make_fastdiv(a.kw);
   dim3 grid(pl.blocks_m, (a.cout + 32 * FM * WM - 1) / (32 * FM * WM));
   hipLaunchKernelGGL((conv_mfma<WM, WN, WK, FM, FN, S, D>), grid,
                      dim3(64 * WM * WN * WK), 0, stream, a);
@@ -553,7 +564,7 @@ bool mfma_eligible(const ConvLaunch& a) {
          (a.in_layout == IFQ_LAYOUT_U2_NHWC_PACKED || a.in_layout == IFQ_LAYOUT_U2_BLOCK64);
 }
 
-// The dispatcher's choice among the three MFMA kernels for one layer, and
+// The dispatcher's choice among the kernels on the MFMA fast path for one layer, and
 // their plans, kept by layer geometry.
 namespace {
 
@@ -565,26 +576,39 @@ struct MfmaChoice {
   Plan pl;
 };
 
-// Layers the windowed kernel of ifq_conv_win.hip is weighed for: not 3x3
-// layers on BLOCK64 codes, which the register-blocked kernels take (batch 7,
-// 72x56x192 -> 128: 9.7 us against 12.3).
-bool win_candidate(const ConvLaunch& a) {
-  return !(a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3);
+// The windowed 3x3 kernel's prediction is a fit to the threshold epilogue with 2-bit
+// codes at one tile a CU; beside other kernels its time by epilogue, fitted to 1002
+// layers that the register-blocked kernels do not take (5% rms on the joins with
+// identity, 7 to 10% on 2-bit codes and sums, 15 to 18% on the others).
+double halo_weigh(const ConvLaunch& a, double t_us) {
+  if (a.join_kind == IFQ_JOIN_CONV) return 1.12 * t_us + 6.4;
+  if (a.out_mode == 0) return t_us - 0.5;
+  if (a.rec != 4) return 1.13 * t_us + 10.9;
+  return a.join_kind == IFQ_JOIN_IDENTITY ? 0.95 * t_us + 4.6 : 0.98 * t_us + 2.0;
 }
 
-// 3x3 layers on BLOCK64 codes with so few outputs that 32 x 64 tiles are at
-// most one per CU: the register-blocked kernels' tiles leave most CUs idle, and
-// the windowed kernel's small ones, K split over the waves, are faster:
-// 13x13x512 -> 512 at batch 1 10.1 -> 8.2 us, at batch 4 11.7 -> 9.4, 14x14x256 ->
-// 256 7.1 -> 6.2, 28x28x128 -> 128 6.3 -> 5.5; past one tile a CU slower
-// (14x14x256 at batch 16 7.9 against 8.9), and with 64 channels too (28x28: 4.7
-// against 5.1, its K is one stage deep).
-bool win_small(const ConvLaunch& a) {
-  return a.in_layout == IFQ_LAYOUT_U2_BLOCK64 && a.kh == 3 && a.kw == 3 && a.stride == 1 &&
-         a.pad == 1 && a.cin >= 128 && a.out_mode == 2 && a.join_kind == IFQ_JOIN_NONE &&
-         (int64_t)((a.m + 63) / 64) * ((a.cout + 31) / 32) <= kNumCUs;
-}
-
+// The kernel predicted fastest, each by a fit to its own measured times, among
+//  - the register-blocked ones (3x3 on BLOCK64 codes, 2-bit codes out), or where they
+//    do not take such a layer the windowed 3x3 one,
+//  - the tiled one,
+//  - conv_win; but not on layers of 64 channels that the register-blocked kernels
+//    take: their K is one stage deep and the prediction too rough for what could be
+//    gained (3.5% on average over 313 layers, 49 of them more than 3% slower;
+//    28x28x64 -> 64 at batch 1: 4.9 us, conv_win 5.2).
+// Beside every kernel and tile, each timed on 6664 layers, the choice is 1.5% behind
+// the fastest on average where the register-blocked kernels do not take the layer and
+// 1.3% where they do. In us on one card:
+//  - few stages on many pixels stay on the tiled kernel: 1x1 28x28x128 -> 512 at batch
+//    16 8.0, conv_win 9.1; 56x56x64 -> 256 at batch 8 8.0, 9.2; 69x67x64 -> 320 sums
+//    at batch 2 6.7, 9.3;
+//  - deeper K goes to conv_win, which does not gather its input tap by tap: 5x5
+//    27x27x128 -> 256 at batch 4 18.9, 10.5; and where the register-blocked tiles leave
+//    CUs idle its small tiles, K split over the waves: 13x13x512 -> 512 at batch 1
+//    11.1, 8.3, 14x14x256 -> 512 strided at batch 2 8.3, 6.4, 7x7x512 -> 512 with an
+//    identity join at batch 16 12.3, 9.8; not where they fill them: 28x28x128 -> 128
+//    with the join at batch 8 7.4, 7.7;
+//  - windows too wide for the register-blocked kernels: strided 64x80x448 -> 448 with
+//    the join, batch 10, on the windowed 3x3 kernel 35.3, conv_win 43.7, tiled 43.3.
 MfmaChoice plan_choice(const ConvLaunch& a) {
   MfmaChoice c{};
   if (fc_eligible(a)) {
@@ -598,23 +622,18 @@ MfmaChoice plan_choice(const ConvLaunch& a) {
     return c;
   }
   c.pl = plan_mfma(a);
-  if (r3 && c.rp.t_us <= c.pl.t_us && (!halo || c.rp.t_us <= c.hp.t_us))
+  c.kind = 2;
+  double t = c.pl.t_us, tw = 0;
+  const bool win = plan_win_us(a, &tw);
+  if (r3 && c.rp.weigh_us <= t) {
     c.kind = 0;
-  else if (halo && c.hp.t_us < c.pl.t_us)
-    c.kind = 1;
-  else
-    c.kind = 2;
-  // by a margin: the tiled kernel's prediction is high on its largest tiles
-  // (64x56x56x64 -> 64 3x3 packed: 26.6 us predicted, 23.9 measured, against
-  // 25.6 and 26.3 for the windowed kernel)
-  double tw = 0;
-  if (win_small(a) && plan_win_us(a, &tw)) {
-    c.kind = 3;
-    return c;
+    t = c.rp.weigh_us;
   }
-  if (win_candidate(a) && plan_win_us(a, &tw) &&
-      tw < 0.85 * (c.kind == 0 ? c.rp.t_us : c.kind == 1 ? c.hp.t_us : c.pl.t_us))
-    c.kind = 3;
+  if (halo && !r3 && halo_weigh(a, c.hp.t_us) < t) {
+    c.kind = 1;
+    t = halo_weigh(a, c.hp.t_us);
+  }
+  if (win && tw < t && !(r3 && a.cin < 128)) c.kind = 3;
   return c;
 }
 
@@ -696,8 +715,7 @@ hipError_t launch_conv_mfma(const ConvLaunch& a, hipStream_t stream) {
     case 2: return launch_variant<1, 8, 1, 2, 2, 2, 4>(a, pl, stream);
     case 3: return launch_variant<2, 4, 1, 1, 2, 2, 6>(a, pl, stream);
     case 4: return launch_variant<2, 2, 2, 2, 2, 2, 3>(a, pl, stream);
-    case 5: return launch_variant<2, 1, 4, 1, 4, 1, 6>(a, pl, stream);
-    default: return launch_variant<1, 1, 8, 1, 1, 1, 6>(a, pl, stream);
+    default: return launch_variant<2, 1, 4, 1, 4, 1, 6>(a, pl, stream);
   }
 }
 

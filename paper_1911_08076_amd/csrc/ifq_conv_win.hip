@@ -953,7 +953,7 @@ bool plan_win_us(const ConvLaunch& a, double* t_us) {
   WinPlan p;
   if (a.m <= 0 || a.pool_k || a.join_kind == IFQ_JOIN_CONV_FUSED || a.f4 || !choose_win(a, &p))
     return false;
-  *t_us = p.t_us;
+  *t_us = p.est_us;
   return true;
 }
 

@@ -131,8 +131,6 @@ struct ConvLaunch {
   int32_t pho, pwo;
   FastDiv div_pwo;     // division by pwo (pooled pixel -> pooled row)
   FastDiv div_pho;     // division by pho (pooled row -> image)
-  FastDiv div_taps;    // tiled kernel: division by kh*kw (K64 step -> channel block)
-  FastDiv div_kw;      // and by kw (tap -> row)
   int32_t wcells;      // register-blocked 3x3 kernels: window cells per channel block
   int32_t tiles_wg;    // persistent 3x3 kernel: consecutive pixel tiles per workgroup
   // K split across workgroups (register-blocked 3x3 kernel, threshold
@@ -372,6 +370,7 @@ struct Reg3Plan {
   W2Plan w2;
   WpPlan wp;
   double t_us;
+  double weigh_us;   // (planned, not forced) to weigh it against the other kernels
 };
 int reg3_variant_count();
 bool reg3_variant_fp4(int v);

@@ -55,7 +55,7 @@ CASES = [
     ("f_5x5_blocks", 4, 27, 27, 128, 256, 5, 1, 2, 2, 2, B64, B64),
     ("f_5x5_s2", 2, 112, 86, 64, 330, 5, 2, 2, 2, 2, B64, I8),
     ("f_1x1_blocks", 5, 19, 23, 320, 192, 1, 2, 0, 2, 2, B64, U2),
-    ("f_1x1_i32", 8, 16, 12, 64, 193, 1, 1, 0, 2, 0, B64, I32),
+    ("f_1x1_i32", 8, 16, 12, 256, 193, 1, 1, 0, 2, 0, B64, I32),
     ("f_wide", 9, 60, 52, 128, 448, 5, 2, 2, 2, 2, B64, B64),
     ("f_even_filter", 3, 20, 18, 192, 48, 4, 1, 2, 2, 4, U2, I8),
 ]

@@ -1,6 +1,7 @@
 """Which kernel the dispatcher takes where two or more cover a layer, on the CPU:
 layers measured with each of them (us in the comments, MI355X), on both sides of
 the line and a few percent or more apart."""
+import numpy as np
 import pytest
 
 import paper_1911_08076_amd as P
@@ -30,3 +31,43 @@ def name(n, h, w, cin, cout, k, stride, in_bits, out_bits, il, ol):
 ])
 def test_general_or_windowed_kernel(layer, kernel):
     assert name(*layer).startswith(kernel), name(*layer)
+
+
+def join_name(n, h, w, cin, cout, stride, join):
+    d = P.conv_desc(n, h, w, cin, cout, 3, stride, 1, 2, 2, B64, B64)
+    return P.ifq_conv_kernel_name(d, join)
+
+
+@pytest.mark.parametrize("layer,kernel", [
+    # tiled and windowed kernel on layers of few stages: 8.0 and 9.1 us
+    ((16, 28, 28, 128, 512, 1, 1, 2, 2, B64, B64), "conv_mfma<1, 8, 1, 2, 2,"),
+    ((8, 56, 56, 64, 256, 1, 1, 2, 2, B64, B64), "conv_mfma<1, 8, 1, 2, 2,"),    # 8.0, 9.2
+    ((1, 165, 152, 256, 256, 1, 1, 2, 2, B64, B64), "conv_mfma<1, 8, 1, 2, 2,"), # 9.7, 10.4
+    ((2, 69, 67, 64, 320, 1, 1, 2, 0, B64, I32), "conv_mfma<2, 4, 1, 1, 2,"),    # 6.7, 9.3
+    ((1, 169, 158, 64, 256, 1, 1, 2, 2, B64, B64), "conv_mfma<1, 8, 1, 2, 2,"),  # 8.2, 9.3
+    # and deeper K: 18.9, 10.5
+    ((4, 27, 27, 128, 256, 5, 1, 2, 2, B64, B64), "conv_win<2,"),
+    ((6, 75, 57, 128, 160, 3, 2, 2, 2, U2, U2), "conv_win<2,"),                  # 12.2, 8.7
+    # 3x3 layers on BLOCK64 codes, register-blocked and windowed kernel: 11.1, 8.3
+    ((1, 13, 13, 512, 512, 3, 1, 2, 2, B64, B64), "conv_win<2,"),
+    ((2, 14, 14, 256, 512, 3, 2, 2, 2, B64, B64), "conv_win<2,"),                # 8.3, 6.4
+    ((2, 45, 44, 448, 192, 3, 1, 2, 2, B64, B64), "conv_win<2,"),                # 26.0, 11.8
+    ((1, 28, 28, 64, 64, 3, 1, 2, 2, B64, B64), "conv_wv<"),                     # 4.9, 5.2
+    ((14, 17, 16, 128, 256, 3, 1, 2, 2, B64, B64), "conv_wv<"),                  # 6.8, 7.7
+    # outputs that the register-blocked kernels do not write: 12.8 tiled, 6.6
+    ((4, 14, 14, 256, 256, 3, 1, 2, 3, B64, I8), "conv_win<2,"),
+    ((2, 54, 54, 512, 448, 3, 1, 2, 0, B64, I32), "conv_halo<"),                 # 23.9, 26.4
+])
+def test_kernels_on_2_bit_codes(layer, kernel):
+    assert name(*layer).startswith(kernel), name(*layer)
+
+
+def test_kernels_with_an_identity_join():
+    table = np.zeros(4, np.int32)    # its address only is looked at
+    j = P.make_join(P.IFQ_JOIN_IDENTITY, B64, table, None, [0.5, 1.0, 1.5], table=table)
+    assert join_name(16, 7, 7, 512, 512, 1, j).startswith("conv_win<2,")      # 12.3 us, 9.8
+    assert join_name(4, 14, 14, 256, 256, 1, j).startswith("conv_win<2,")     # 7.6, 6.8
+    assert join_name(8, 28, 28, 128, 128, 1, j).startswith("conv_w")          # 7.4, 7.7
+    assert not join_name(8, 28, 28, 128, 128, 1, j).startswith("conv_win<")
+    # windows too wide for the register-blocked kernels: 35.3, conv_win 43.7
+    assert join_name(10, 80, 64, 448, 448, 2, j).startswith("conv_halo<")

@@ -543,7 +543,8 @@ IFQ_API const char* ifq_conv_fp4_kernel_name(const ifq_conv_desc* d, const ifq_j
  * ifq_conv_pool_forward with the contraction on the fp4 path (as
  * ifq_conv_forward_fp4; w_fp4 from ifq_pack_weights_fp4): the same pooled
  * codes. Covered where both a fused-pool plan and an fp4 instance of the
- * windowed kernel exist; otherwise UNSUPPORTED (the name query returns "").
+ * windowed 3x3 kernel exist, and run there or on conv_w2, whichever is predicted
+ * faster; otherwise UNSUPPORTED (the name query returns "").
  * Errors: INVALID_ARGUMENT, UNSUPPORTED, HIP.
  */
 IFQ_API ifq_status ifq_conv_pool_forward_fp4(const ifq_conv_desc* d, const ifq_pool_desc* p,

@@ -673,19 +673,17 @@ int64_t conv_mfma_workspace_bytes(const ConvLaunch& a) {
   return w2_split_bytes(a, c.rp.w2);
 }
 
-// A fused pool the windowed kernel covers: conv_w2 where its prediction is below
-// the windowed kernel's by the margin that the pooling itself takes of its
-// lead (28x28x512 -> 512 at batch 16, predicted at 0.92: 35.4 against 35.3-36.3
-// us; 26x26x128 -> 256 at batch 4, 0.91: 9.1 against 8.8), and its tiles fill half
-// of the CUs. Smaller launches stay where they were: the windowed kernel's
-// pooled instances are what the tests at those sizes cover, though conv_w2
-// measures faster on them too with 256 channels or more (28x28x512 -> 512 at
-// batch 2 12.3 against 19.9 us) and even with 64 (7.0-7.2 both).
+// A fused pool the windowed 3x3 kernel covers: conv_w2 where its prediction is below
+// the windowed kernel's by the margin that the pooling itself takes of its lead (its
+// prediction is of the unpooled layer, 11% below the pooled one's time). Over 905 int8
+// layers timed on both the choice is 0.4% behind the faster one on average and 10% at
+// most; with the bound at 0.85 or 0.95 of it 0.9% and 22%, 0.5% and 10%. Over 521 fp4
+// layers conv_w2 is never more than 5% slower. us: 28x28x512 -> 512 at batch 2 20.8 on
+// the windowed kernel, 12.2 on conv_w2; 28x36x448 -> 256 at batch 9 25.8, 33.0.
 namespace {
 
 bool pool_on_w2(const ConvLaunch& a, const HaloPlan& hp, Reg3Plan* rp) {
-  if (!plan_reg3(a, -1, rp) || rp->persistent || rp->t_us >= 0.9 * hp.t_us) return false;
-  return w2_tiles(a, rp->w2) >= kNumCUs / 2;
+  return plan_reg3(a, -1, rp) && !rp->persistent && rp->t_us < 0.9 * hp.t_us;
 }
 
 }  // namespace

@@ -763,16 +763,12 @@ bool w2_fit(const ConvLaunch& a, int v, W2Plan* out, int want_split) {
 
 int w2_variant_count() { return kNumW2; }
 
-int64_t w2_tiles(const ConvLaunch& a, const W2Plan& p) {
-  const int64_t bm = 32 * kW2Variants[p.variant].fm * kW2Variants[p.variant].wm;
-  return p.blocks_m * ((a.cout + bm - 1) / bm);
-}
-
 int64_t w2_split_bytes(const ConvLaunch& a, const W2Plan& p) {
   if (p.ksplit <= 1) return 0;
   const W2Variant& V = kW2Variants[p.variant];
   const int64_t bm = 32 * V.fm * V.wm, bn = 32 * V.fn * V.wn;
-  return kSplitCounterBytes + w2_tiles(a, p) * p.ksplit * bm * bn * 4;
+  const int64_t tiles = (int64_t)p.blocks_m * ((a.cout + bm - 1) / bm);
+  return kSplitCounterBytes + tiles * p.ksplit * bm * bn * 4;
 }
 bool w2_variant_fp4(int v) { return v >= 0 && v < kNumW2 && kW2Variants[v].f4; }
 

@@ -335,7 +335,6 @@ constexpr int64_t kSplitCounterBytes = 64 << 10;
 constexpr int64_t kSplitMaxTiles = kSplitCounterBytes / 4;
 // Workspace bytes of a K-split launch of plan p (0 without a split).
 int64_t w2_split_bytes(const ConvLaunch& a, const W2Plan& p);
-int64_t w2_tiles(const ConvLaunch& a, const W2Plan& p);   // workgroup tiles of plan p
 int w2_variant_count();
 bool w2_variant_fp4(int v);   // variant v runs the fp4 contraction (fp4 weight blob)
 // want_split > 0: only plans with that K split (a.split_ok must be set for

@@ -116,23 +116,43 @@ def test_small2_conv_pool_bit_exact(P, case):
     check(P, name, L, n, k, U2, outs, "conv_small2<")
 
 
-# name, n, h, w, c_in, c_out, pool k, output layouts
+# layers the windowed 3x3 kernel keeps beside the register-blocked one, each of its
+# pooled instances (name, n, h, w, c_in, c_out, stride, pool k, layouts, kernel)
 HALO_POOL = [
-    ("hp_yolo_c4", 2, 52, 52, 64, 128, 2, [B64, U2, I8]),
-    ("hp_yolo_c5", 2, 26, 26, 128, 256, 2, [B64]),
-    ("hp_vgg_conv2_2", 1, 112, 112, 128, 128, 2, [B64]),
-    ("hp_vgg_conv4_3", 2, 28, 28, 512, 512, 2, [B64, U2]),
-    ("hp_vgg_conv5_3_spans_images", 3, 14, 14, 512, 512, 2, [B64]),
-    ("hp_c64_out64", 4, 56, 56, 64, 64, 2, [B64, I8]),
-    ("hp_pool4", 2, 24, 24, 128, 128, 4, [B64]),
+    ("hp_yolo_c4", 2, 52, 52, 64, 128, 1, 2, [B64, U2], "conv_halo<8, 1, 6, false, 2, true, false>"),
+    ("hp_yolo_c4_bytes", 2, 52, 52, 64, 128, 1, 2, [I8],
+     "conv_halo<8, 1, 6, false, 2, false, false>"),
+    ("hp_yolo_c5", 2, 26, 26, 128, 256, 1, 2, [B64], "conv_halo<4, 2, 4, false, 4, true, false>"),
+    ("hp_yolo_c5_bytes", 2, 26, 26, 128, 256, 1, 2, [I8],
+     "conv_halo<4, 2, 4, false, 4, false, false>"),
+    ("hp_c64_out64", 4, 56, 56, 64, 64, 1, 2, [B64], "conv_halo<8, 1, 6, false, 2, true, false>"),
+    ("hp_pool4", 2, 24, 24, 128, 128, 1, 4, [B64], "conv_halo<4, 2, 4, false, 4, true, false>"),
+    ("hp_s2_wide_rows", 1, 23, 83, 448, 128, 2, 2, [B64, U2],
+     "conv_halo<8, 1, 6, false, 4, true, false>"),
+    ("hp_s2_bytes", 2, 83, 47, 512, 16, 2, 3, [I8], "conv_halo<8, 1, 6, false, 4, false, false>"),
+    ("hp_k_split_4", 1, 18, 6, 256, 176, 1, 3, [I8], "conv_halo<2, 4, 4, false, 4, false, false>"),
 ]
 
 
 @pytest.mark.parametrize("case", HALO_POOL, ids=[c[0] for c in HALO_POOL])
 def test_halo_conv_pool_bit_exact(P, case):
-    name, n, h, w, cin, cout, k, outs = case
-    L = make_layer(name, h, w, cin, cout, 3, 1, 1, 2, 2)
-    check(P, name, L, n, k, B64, outs, "conv_halo<")
+    name, n, h, w, cin, cout, st, k, outs, kernel = case
+    L = make_layer(name, h, w, cin, cout, 3, st, 1, 2, 2)
+    check(P, name, L, n, k, B64, outs, kernel)
+
+
+# (name, n, h, w, c_in, c_out, stride, pool k, kernel)
+HALO_POOL_FP4 = [
+    ("hp4_wide_rows", 1, 23, 83, 448, 128, 2, 2, "conv_halo<8, 1, 6, false, 4, true, true>"),
+    ("hp4_k_split_2", 4, 7, 63, 512, 192, 2, 4, "conv_halo<4, 2, 4, false, 4, true, true>"),
+]
+
+
+@pytest.mark.parametrize("case", HALO_POOL_FP4, ids=[c[0] for c in HALO_POOL_FP4])
+def test_halo_conv_pool_fp4_bit_exact(P, case):
+    name, n, h, w, cin, cout, st, k, kernel = case
+    L = make_layer(name, h, w, cin, cout, 3, st, 1, 2, 2)
+    check(P, name, L, n, k, B64, [B64], kernel, fp4=True)
 
 
 # windows that overlap, run in SAME mode or do not tile the output: each tile
@@ -165,11 +185,15 @@ def test_small2_conv_pool_whole_images(P):
     check(P, "s2p_pool2s1_same", L, 3, 2, U2, [B64, U2], "conv_small2<", 1, "same")
 
 
-# launches that fill half of the CUs, on the register-blocked kernel: one and
-# two workgroups per CU, K groups, tiles of one window row and of several, a
+# layers on the register-blocked kernel, from a few workgroups to two per CU: K groups,
+# tiles of one window row and of several, a
 # last tile with fewer, tiles that span images, a ragged channel block, larger
 # windows, a strided conv (name, n, h, w, c_in, c_out, stride, pool k, layouts)
 W2_POOL = [
+    ("wp_one_image_112", 1, 112, 112, 128, 128, 1, 2, [B64]),
+    ("wp_vgg_two_images", 2, 28, 28, 512, 512, 1, 2, [B64, U2]),
+    ("wp_vgg_three_images_span", 3, 14, 14, 512, 512, 1, 2, [B64]),
+    ("wp_few_tiles", 1, 8, 8, 512, 64, 1, 2, [B64, U2]),
     ("wp_yolo_c4", 8, 52, 52, 64, 128, 1, 2, [B64, U2]),
     ("wp_26", 17, 26, 26, 256, 256, 1, 2, [B64]),
     ("wp_vgg_conv2_2", 3, 112, 112, 128, 128, 1, 2, [B64]),

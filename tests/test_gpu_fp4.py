@@ -79,8 +79,8 @@ def test_fp4_offered_for_the_64_channel_tiles(P):
     d = P.conv_desc(64, 56, 56, 64, 64, 3, 1, 1, 2, 2, B64, B64)
     assert P.ifq_conv_kernel_name(d) == "conv_wv<0, false, 73728, 80896>"
     assert P.ifq_conv_fp4_kernel_name(d) == "conv_wv<0, true, 36864, 114688>"
-    # a fused pool is not the register-blocked kernel's: the windowed
-    # kernel's fp4 instances take it
+    # with a fused pool fp4 is offered where the windowed kernel's int8 tile has an
+    # fp4 instance, which its 64-channel one has not
     pd = P.pool_desc(64, 56, 56, 64, 2, 2, P.IFQ_POOL_VALID, 2, B64)
     assert P.ifq_conv_pool_fp4_kernel_name(d, pd) in ("",) or \
         P.ifq_conv_pool_fp4_kernel_name(d, pd).startswith("conv_halo<")
@@ -188,7 +188,7 @@ def test_fp4_conv_pool_bit_exact(P, case):
     d = P.conv_desc(n, h, h, cin, cout, 3, 1, 1, 2, 2, B64, B64)
     pd = P.pool_desc(n, h, h, cout, 2, 2, P.IFQ_POOL_VALID, 2, B64)
     kname = P.ifq_conv_pool_fp4_kernel_name(d, pd)
-    assert kname.endswith(", true, true>"), kname
+    assert kname.startswith("conv_w2<") and P.kernel_is_fp4(kname), kname
     w4 = to_dev(P.ifq_pack_weights_fp4(d, p["w"]))
     xd = upload_codes(P, x, B64)
     ob = P.ifq_tensor_bytes(n, h // 2, h // 2, cout, B64)

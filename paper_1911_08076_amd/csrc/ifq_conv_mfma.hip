@@ -1,6 +1,8 @@
 // Fast path of the integrated fixed-point quantized convolution on gfx950
 // (MI355X): 2-bit input codes with c_in a multiple of 64, in the BLOCK64 or
-// the NHWC packed layout.
+// the NHWC packed layout. The tiled kernel (conv_mfma), which the next paragraphs
+// are about, the one for fully connected layers (conv_fc, further down), and the
+// choice among them and the other kernels of the fast path (plan_choice).
 //
 // The integer part of Eq. (1), a = W_b (x) X_q, is an implicit GEMM
 // D[co][pixel] = sum_k W[co][k] * X[pixel][k] on v_mfma_i32_32x32x32_i8:
@@ -316,7 +318,7 @@ struct FcGeom {
 };
 
 template <int NB>
-__global__ __launch_bounds__(512) void conv_mfma(ConvLaunch a, FcGeom g) {
+__global__ __launch_bounds__(512) void conv_fc(ConvLaunch a, FcGeom g) {
   constexpr int NW = 8, U = 3;
   constexpr int SUMS = NW * NB * 1024;
   __shared__ __attribute__((aligned(16))) uint8_t lds[SUMS + 1024];
@@ -442,7 +444,7 @@ int fc_blocks(const ConvLaunch& a) { return a.m <= 16 ? 1 : a.m <= 32 ? 2 : 4; }
 
 const char* fc_name(const ConvLaunch& a) {
   const int nb = fc_blocks(a);
-  return nb == 1 ? "conv_mfma<1>" : nb == 2 ? "conv_mfma<2>" : "conv_mfma<4>";
+  return nb == 1 ? "conv_fc<1>" : nb == 2 ? "conv_fc<2>" : "conv_fc<4>";
 }
 
 hipError_t launch_fc(const ConvLaunch& a, hipStream_t stream) {
@@ -456,9 +458,9 @@ hipError_t launch_fc(const ConvLaunch& a, hipStream_t stream) {
   const int nb = fc_blocks(a);
   const dim3 grid((a.cout + 15) / 16, (a.m + 16 * nb - 1) / (16 * nb));
   switch (nb) {
-    case 1: hipLaunchKernelGGL((conv_mfma<1>), grid, dim3(512), 0, stream, a, g); break;
-    case 2: hipLaunchKernelGGL((conv_mfma<2>), grid, dim3(512), 0, stream, a, g); break;
-    default: hipLaunchKernelGGL((conv_mfma<4>), grid, dim3(512), 0, stream, a, g); break;
+    case 1: hipLaunchKernelGGL((conv_fc<1>), grid, dim3(512), 0, stream, a, g); break;
+    case 2: hipLaunchKernelGGL((conv_fc<2>), grid, dim3(512), 0, stream, a, g); break;
+    default: hipLaunchKernelGGL((conv_fc<4>), grid, dim3(512), 0, stream, a, g); break;
   }
   return hipGetLastError();
 }

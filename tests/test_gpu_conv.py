@@ -75,11 +75,11 @@ FC_U2 = [("fc6_u2", 32, 6, 6, 256, 4096, 6), ("fc7_u2", 32, 1, 1, 4096, 4096, 1)
 
 @pytest.mark.parametrize("case", FC_U2, ids=[c[0] for c in FC_U2])
 def test_fc_as_conv_on_mfma_path(P, case):
-    # the same layers from 2-bit packed codes: the MFMA kernel takes any kh x kw
+    # the same layers from 2-bit packed codes: the fully connected kernel
     name, n, h, w, cin, cout, k = case
     L = make_layer(name, h, w, cin, cout, k, 1, 0, 2, 2)
     d = P.conv_desc(n, h, w, cin, cout, k, 1, 0, 2, 2, U2, U2)
-    assert P.ifq_conv_kernel_name(d).startswith("conv_mfma<")
+    assert P.ifq_conv_kernel_name(d) == "conv_fc<2>"
     seed = zlib.crc32(name.encode()) % 997
     p = params_for(seed, L)
     x = codes_for(seed, (n, h, w, cin), 2)

@@ -42,7 +42,7 @@ def test_fc_bit_exact(P, case, dump):
     if h == w:
         L = make_layer(name, h, w, cin, cout, h, 1, 0, 2, ob)
         d = P.conv_desc(n, h, w, cin, cout, h, 1, 0, 2, ob, il, ol)
-        assert P.ifq_conv_kernel_name(d) == "conv_mfma<%d>" % (1 if n <= 16 else 2 if n <= 32 else 4)
+        assert P.ifq_conv_kernel_name(d) == "conv_fc<%d>" % (1 if n <= 16 else 2 if n <= 32 else 4)
     else:
         # a rectangular window as a square filter over a zero-padded square
         # image is another layer; the descriptor takes kw on its own
@@ -72,7 +72,7 @@ def rectangular(P, case, dump):
     for i in range(1, 1 << ob):
         want += (sums * s > rec[:, i]).astype(np.uint8).reshape(want.shape)
     d = P.conv_desc(n, h, w, cin, cout, h, 1, 0, 2, ob, il, ol, kw=w)
-    assert P.ifq_conv_kernel_name(d).startswith("conv_mfma<")
+    assert P.ifq_conv_kernel_name(d) == "conv_fc<%d>" % (1 if n <= 16 else 2 if n <= 32 else 4)
     acc = torch.empty(n * cout, dtype=torch.int32, device=device()) if dump else None
     y = torch.empty(P.ifq_tensor_bytes(n, 1, 1, cout, ol), dtype=torch.uint8, device=device())
     P.ifq_conv_forward(d, upload_codes(P, x, il), to_dev(P.ifq_pack_weights(d, wt)),

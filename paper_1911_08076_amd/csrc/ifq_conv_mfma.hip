@@ -591,7 +591,7 @@ double halo_weigh(const ConvLaunch& a, double t_us) {
 
 // The kernel predicted fastest, each by a fit to its own measured times, among
 //  - the register-blocked ones (3x3 on BLOCK64 codes, 2-bit codes out), or where they
-//    do not take such a layer the windowed 3x3 one,
+//    do not take such a layer in one piece the windowed 3x3 one,
 //  - the tiled one,
 //  - conv_win; but not on layers of 64 channels that the register-blocked kernels
 //    take: their K is one stage deep and the prediction too rough for what could be
@@ -631,7 +631,10 @@ MfmaChoice plan_choice(const ConvLaunch& a) {
     c.kind = 0;
     t = c.rp.weigh_us;
   }
-  if (halo && !r3 && halo_weigh(a, c.hp.t_us) < t) {
+  // (a plan that splits K across workgroups needs a workspace and is the register-blocked
+  // kernels' only one on its layer)
+  const bool split = r3 && !c.rp.persistent && c.rp.w2.ksplit > 1;
+  if (halo && (!r3 || split) && halo_weigh(a, c.hp.t_us) < t) {
     c.kind = 1;
     t = halo_weigh(a, c.hp.t_us);
   }

@@ -71,3 +71,12 @@ def test_kernels_with_an_identity_join():
     assert not join_name(8, 28, 28, 128, 128, 1, j).startswith("conv_win<")
     # windows too wide for the register-blocked kernels: 35.3, conv_win 43.7
     assert join_name(10, 80, 64, 448, 448, 2, j).startswith("conv_halo<")
+
+
+@pytest.mark.parametrize("layer", [(16, 8, 64, 1024, 480), (10, 19, 64, 1152, 256),
+                                   (6, 59, 64, 1152, 128), (5, 39, 39, 1024, 128)])
+def test_no_layer_comes_to_need_a_workspace(layer):
+    # where the register-blocked kernels take a layer only split over K, another kernel
+    # that needs no workspace is faster
+    n, h, w, ci, co = layer
+    assert P.ifq_conv_workspace_bytes(P.conv_desc(n, h, w, ci, co, 3, 1, 1, 2, 2, B64, U2)) == 0

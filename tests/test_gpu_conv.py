@@ -218,8 +218,58 @@ def test_conv_packed_layouts_bit_exact(P, case, io):
     run_layout_case(P, case, io)
 
 
-# shapes of the fast path (c_in % 64 == 0): every tile variant, ragged pixel
-# and channel tiles, stride 2, 1x1 and 5x5 filters, the judged ResNet shapes
+# the tiled kernel on its own layers, each of its tiles: ragged pixel and channel
+# tiles, rows past the last tile's, one stage and many, sums and codes
+# (name, n, h, w, cin, cout, k, stride, pad, out_bits, in, out, template arguments)
+TILED = [
+    ("t_128x512_i32", 34, 50, 46, 64, 76, 1, 1, 0, 0, U2, I32, "2, 4, 1, 2, 4, 1, 6"),
+    ("t_128x256_i32", 22, 158, 33, 64, 593, 1, 3, 0, 0, U2, I32, "2, 4, 1, 2, 2, 2, 4"),
+    ("t_64x512", 1, 169, 158, 64, 256, 1, 1, 0, 2, B64, B64, "1, 8, 1, 2, 2, 2, 4"),
+    ("t_64x512_bytes", 8, 113, 87, 64, 35, 1, 1, 0, 2, B64, I8, "1, 8, 1, 2, 2, 2, 4"),
+    ("t_64x256_i32", 2, 69, 67, 64, 320, 1, 1, 0, 0, B64, I32, "2, 4, 1, 1, 2, 2, 6"),
+    ("t_64x256_few_pixels", 9, 2, 2, 128, 27, 1, 3, 0, 0, U2, I32, "2, 4, 1, 1, 2, 2, 6"),
+    ("t_128x128_k_split_2", 57, 77, 7, 128, 584, 2, 2, 0, 0, U2, I32, "2, 2, 2, 2, 2, 2, 3"),
+    ("t_64x128_k_split_4", 1, 147, 116, 768, 1, 2, 4, 1, 1, U2, I8, "2, 1, 4, 1, 4, 1, 6"),
+    ("t_64x128_k_split_4_i32", 30, 72, 70, 640, 15, 2, 3, 1, 0, U2, I32, "2, 1, 4, 1, 4, 1, 6"),
+]
+
+
+@pytest.mark.parametrize("case", TILED, ids=[c[0] for c in TILED])
+@pytest.mark.parametrize("dump", [True, False], ids=["sums", "codes"])
+def test_tiled_bit_exact(P, case, dump):
+    name, n, h, w, cin, cout, k, st, pad, ob, il, ol, tile = case
+    L = make_layer(name, h, w, cin, cout, k, st, pad, 2, ob)
+    d = P.conv_desc(n, h, w, cin, cout, k, st, pad, 2, ob, il, ol)
+    assert P.ifq_conv_kernel_name(d) == "conv_mfma<%s>" % tile
+    seed = zlib.crc32(name.encode()) % 997
+    p = params_for(seed, L)
+    x = codes_for(seed, (n, h, w, cin), 2)
+    want_acc, want = oracle_layer(L, x, p)
+    acc, got = gpu_layer(P, L, n, x, p, in_layout=il, out_layout=ol, dump=dump)
+    assert not dump or np.array_equal(acc, want_acc)
+    assert np.array_equal(got, expect_layout(want, ol) if ob else want)
+
+
+@pytest.mark.parametrize("n,h,w,cin,cout,st,lay,tile", [
+    (29, 9, 56, 64, 384, 2, U2, "2, 4, 1, 1, 2, 2, 6"),
+    (32, 22, 31, 64, 192, 1, B64, "1, 8, 1, 2, 2, 2, 4")])
+def test_tiled_identity_join(P, n, h, w, cin, cout, st, lay, tile):
+    L = make_layer("tj", h, w, cin, cout, 1, st, 0, 2, 2, join=("identity", "x"))
+    p = params_for(31, L)
+    ho, wo = (h - 1) // st + 1, (w - 1) // st + 1
+    x, sc = codes_for(31, (n, h, w, cin), 2), codes_for(32, (n, ho, wo, cout), 2)
+    table = np.zeros(4, np.int32)    # for the name query only
+    join = P.make_join(P.IFQ_JOIN_IDENTITY, lay, table, None, [0.5, 1.0, 1.5], table=table)
+    d = P.conv_desc(n, h, w, cin, cout, 1, st, 0, 2, 2, lay, lay)
+    assert P.ifq_conv_kernel_name(d, join) == "conv_mfma<%s>" % tile
+    want_acc, want = oracle_layer(L, x, p, shortcut=sc)
+    acc, got = gpu_layer(P, L, n, x, p, in_layout=lay, out_layout=lay, shortcut=sc, sc_layout=lay)
+    assert np.array_equal(acc, want_acc)
+    assert np.array_equal(got, expect_layout(want, lay))
+
+
+# shapes of the fast path (c_in % 64 == 0): ragged pixel and channel tiles, stride 2,
+# 1x1 and 5x5 filters, the ResNet shapes, on whichever kernel takes each
 B64_LAYERS = [
     ("b64_3x3_64", 2, 14, 14, 64, 64, 3, 1, 1),
     ("b64_stride2_128", 2, 15, 15, 64, 128, 3, 2, 1),

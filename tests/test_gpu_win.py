@@ -22,52 +22,65 @@ def P():
     return P
 
 
-# (name, n, h, w, cin, cout, k, stride, pad, in_bits, out_bits, in, out)
+# (name, n, h, w, cin, cout, k, stride, pad, in_bits, out_bits, in, out, template
+# arguments of the instance that runs it). Every tile with every kind of input is here.
 CASES = [
-    ("one_pixel", 1, 1, 1, 16, 80, 1, 1, 0, 2, 2, I8, I8),
-    ("all_padding_taps", 3, 1, 1, 32, 33, 3, 1, 1, 4, 4, I8, I8),
-    ("pad_wider_than_filter", 2, 3, 4, 16, 20, 3, 2, 4, 3, 3, I8, I8),
-    ("stride_past_filter", 2, 13, 11, 48, 40, 2, 3, 0, 2, 2, I8, U2),
-    ("images_per_tile", 37, 3, 3, 64, 64, 3, 1, 1, 2, 2, I8, B64),
-    ("chunks_of_64", 2, 21, 19, 512, 96, 3, 1, 1, 2, 2, I8, I8),
-    ("three_window_buffers", 3, 28, 28, 384, 128, 3, 1, 1, 7, 2, I8, U2),
-    ("one_chunk_odd_units", 2, 9, 8, 304, 24, 3, 1, 1, 5, 1, I8, I8),
-    ("wide_tile", 3, 57, 61, 96, 144, 5, 1, 2, 4, 4, I8, I8),
-    ("k_split_8", 4, 7, 7, 512, 80, 3, 1, 1, 1, 3, I8, I8),
-    ("1x1_s2_i32", 5, 17, 15, 80, 72, 1, 2, 0, 4, 0, I8, I32),
-    ("even_filter", 2, 10, 12, 32, 16, 4, 2, 1, 2, 4, I8, I8),
-    ("units_past_c_in", 2, 45, 43, 368, 128, 3, 2, 1, 2, 4, I8, I8),
-    ("tile_128x256", 8, 81, 76, 32, 96, 1, 1, 0, 2, 4, I8, I8),
-    ("tile_128x64", 13, 19, 18, 96, 352, 1, 1, 0, 2, 2, I8, U2),
-    ("tile_64x256", 3, 81, 81, 240, 141, 1, 1, 0, 2, 4, I8, I8),
-    ("tile_64x128", 8, 81, 80, 80, 144, 1, 2, 0, 4, 4, I8, I8),
-    ("tile_32x256", 21, 13, 13, 16, 304, 3, 1, 1, 2, 2, I8, I8),
-    ("tile_64x64", 3, 45, 44, 160, 237, 1, 1, 0, 4, 4, I8, I8),
-    ("tile_32x64", 3, 9, 8, 368, 304, 5, 2, 2, 2, 4, I8, I8),
-    ("u2_one_unit", 2, 23, 31, 16, 80, 3, 1, 1, 2, 2, U2, U2),
-    ("u2_odd_units", 3, 12, 10, 240, 100, 3, 2, 1, 2, 2, U2, U2),
-    ("u2_5x5", 3, 27, 27, 96, 256, 5, 1, 2, 2, 2, U2, B64),
-    ("u2_k_bits_out", 2, 9, 9, 48, 70, 3, 1, 1, 2, 4, U2, I8),
-    ("u2_i32", 2, 9, 9, 176, 30, 1, 1, 0, 2, 0, U2, I32),
-    # weights in fragment order (c_in % 64 == 0), both 2-bit layouts
-    ("f_3x3_s2", 6, 75, 57, 128, 160, 3, 2, 1, 2, 2, U2, U2),
-    ("f_images_per_tile", 9, 7, 7, 512, 512, 3, 1, 1, 2, 2, U2, B64),
-    ("f_5x5_blocks", 4, 27, 27, 128, 256, 5, 1, 2, 2, 2, B64, B64),
-    ("f_5x5_s2", 2, 112, 86, 64, 330, 5, 2, 2, 2, 2, B64, I8),
-    ("f_1x1_blocks", 5, 19, 23, 320, 192, 1, 2, 0, 2, 2, B64, U2),
-    ("f_1x1_i32", 8, 16, 12, 256, 193, 1, 1, 0, 2, 0, B64, I32),
-    ("f_wide", 9, 60, 52, 128, 448, 5, 2, 2, 2, 2, B64, B64),
-    ("f_even_filter", 3, 20, 18, 192, 48, 4, 1, 2, 2, 4, U2, I8),
+    ("one_pixel", 1, 1, 1, 16, 80, 1, 1, 0, 2, 2, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("all_padding_taps", 3, 1, 1, 32, 33, 3, 1, 1, 4, 4, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("pad_wider_than_filter", 2, 3, 4, 16, 20, 3, 2, 4, 3, 3, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("stride_past_filter", 2, 13, 11, 48, 40, 2, 3, 0, 2, 2, I8, U2, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("images_per_tile", 37, 3, 3, 64, 64, 3, 1, 1, 2, 2, I8, B64, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("chunks_of_64", 2, 21, 19, 512, 96, 3, 1, 1, 2, 2, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("three_window_buffers", 3, 28, 28, 384, 128, 3, 1, 1, 7, 2, I8, U2, "0, 1, 2, 4, 1, 1, 2, 3"),
+    ("one_chunk_odd_units", 2, 9, 8, 304, 24, 3, 1, 1, 5, 1, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("5x5_s1_wide", 3, 57, 61, 96, 144, 5, 1, 2, 4, 4, I8, I8, "0, 1, 4, 2, 1, 2, 2, 3"),
+    ("k_split_8", 4, 7, 7, 512, 80, 3, 1, 1, 1, 3, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("1x1_s2_i32", 5, 17, 15, 80, 72, 1, 2, 0, 4, 0, I8, I32, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("even_filter", 2, 10, 12, 32, 16, 4, 2, 1, 2, 4, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("units_past_c_in", 2, 45, 43, 368, 128, 3, 2, 1, 2, 4, I8, I8, "0, 1, 2, 4, 1, 1, 1, 4"),
+    ("tile_128x256", 8, 81, 76, 32, 96, 1, 1, 0, 2, 4, I8, I8, "0, 2, 4, 1, 2, 2, 2, 3"),
+    ("tile_128x64", 13, 19, 18, 96, 352, 1, 1, 0, 2, 2, I8, U2, "0, 2, 2, 2, 2, 1, 2, 3"),
+    ("tile_64x256", 3, 81, 81, 240, 141, 1, 1, 0, 2, 4, I8, I8, "0, 1, 4, 2, 2, 2, 2, 3"),
+    ("tile_64x128", 8, 81, 80, 80, 144, 1, 2, 0, 4, 4, I8, I8, "0, 1, 4, 2, 2, 1, 2, 3"),
+    ("tile_32x256", 21, 13, 13, 16, 304, 3, 1, 1, 2, 2, I8, I8, "0, 1, 4, 2, 1, 2, 2, 3"),
+    ("tile_128x64_4_bits", 3, 45, 44, 160, 237, 1, 1, 0, 4, 4, I8, I8, "0, 2, 2, 2, 2, 1, 2, 3"),
+    ("k_split_8_5x5_s2", 3, 9, 8, 368, 304, 5, 2, 2, 2, 4, I8, I8, "0, 1, 1, 8, 1, 1, 1, 3"),
+    ("u2_one_unit", 2, 23, 31, 16, 80, 3, 1, 1, 2, 2, U2, U2, "1, 1, 1, 8, 1, 1, 1, 3"),
+    ("u2_odd_units", 3, 12, 10, 240, 100, 3, 2, 1, 2, 2, U2, U2, "1, 1, 1, 8, 1, 1, 1, 3"),
+    ("u2_5x5", 3, 27, 27, 96, 256, 5, 1, 2, 2, 2, U2, B64, "1, 1, 2, 4, 1, 1, 2, 3"),
+    ("u2_k_bits_out", 2, 9, 9, 48, 70, 3, 1, 1, 2, 4, U2, I8, "1, 1, 1, 8, 1, 1, 1, 3"),
+    ("u2_i32", 2, 9, 9, 176, 30, 1, 1, 0, 2, 0, U2, I32, "1, 1, 1, 8, 1, 1, 1, 3"),
+    ("f_3x3_s2", 6, 75, 57, 128, 160, 3, 2, 1, 2, 2, U2, U2, "2, 1, 4, 2, 2, 1, 2, 3"),
+    ("f_images_per_tile", 9, 7, 7, 512, 512, 3, 1, 1, 2, 2, U2, B64, "2, 1, 1, 8, 1, 1, 1, 3"),
+    ("f_5x5_blocks", 4, 27, 27, 128, 256, 5, 1, 2, 2, 2, B64, B64, "2, 1, 2, 4, 1, 1, 2, 3"),
+    ("f_5x5_s2", 2, 112, 86, 64, 330, 5, 2, 2, 2, 2, B64, I8, "2, 1, 4, 2, 2, 1, 2, 3"),
+    ("f_1x1_blocks", 5, 19, 23, 320, 192, 1, 2, 0, 2, 2, B64, U2, "2, 1, 1, 8, 1, 1, 1, 3"),
+    ("f_1x1_i32", 8, 16, 12, 256, 193, 1, 1, 0, 2, 0, B64, I32, "2, 1, 2, 4, 1, 1, 1, 4"),
+    ("f_wide", 9, 60, 52, 128, 448, 5, 2, 2, 2, 2, B64, B64, "2, 1, 4, 2, 1, 2, 2, 3"),
+    ("f_even_filter", 3, 20, 18, 192, 48, 4, 1, 2, 2, 4, U2, I8, "2, 1, 1, 8, 1, 1, 1, 3"),
+    ("tile_64x64", 2, 83, 78, 16, 367, 1, 3, 0, 3, 2, I8, I8, "0, 1, 2, 4, 2, 1, 1, 3"),
+    ("tile_32x64", 31, 18, 15, 96, 1, 2, 1, 1, 4, 2, I8, I8, "0, 1, 2, 4, 1, 1, 2, 3"),
+    ("u2_tile_128x256", 17, 54, 51, 16, 330, 1, 2, 0, 2, 4, U2, I8, "1, 2, 4, 1, 2, 2, 2, 3"),
+    ("u2_tile_128x64", 4, 100, 67, 16, 384, 2, 3, 1, 2, 2, U2, I8, "1, 2, 2, 2, 2, 1, 2, 3"),
+    ("u2_tile_64x256", 44, 115, 120, 48, 34, 2, 4, 1, 2, 4, U2, I8, "1, 1, 4, 2, 2, 2, 2, 3"),
+    ("u2_tile_64x128", 7, 31, 31, 32, 172, 1, 1, 0, 2, 3, U2, I8, "1, 1, 4, 2, 2, 1, 2, 3"),
+    ("u2_tile_32x256", 13, 32, 24, 16, 448, 1, 2, 0, 2, 3, U2, I8, "1, 1, 4, 2, 1, 2, 2, 3"),
+    ("u2_tile_64x64", 6, 75, 51, 16, 73, 1, 2, 0, 2, 1, U2, I8, "1, 1, 2, 4, 2, 1, 1, 3"),
+    ("u2_tile_32x64", 2, 50, 34, 16, 73, 1, 1, 0, 2, 2, U2, I8, "1, 1, 2, 4, 1, 1, 1, 4"),
+    ("f_tile_128x256", 47, 21, 19, 64, 197, 1, 1, 0, 2, 2, U2, I8, "2, 2, 4, 1, 2, 2, 2, 3"),
+    ("f_tile_128x64", 9, 21, 17, 64, 640, 1, 1, 0, 2, 2, U2, B64, "2, 2, 2, 2, 2, 1, 2, 3"),
+    ("f_tile_64x256", 25, 116, 108, 64, 37, 2, 3, 0, 2, 4, U2, I8, "2, 1, 4, 2, 2, 2, 2, 3"),
+    ("f_tile_64x64", 6, 23, 17, 64, 197, 1, 1, 0, 2, 2, U2, I8, "2, 1, 2, 4, 2, 1, 1, 3"),
 ]
 
 
 @pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
 @pytest.mark.parametrize("dump", [True, False], ids=["sums", "codes"])
 def test_conv_win_bit_exact(P, case, dump):
-    name, n, h, w, cin, cout, k, st, pad, ib, ob, il, ol = case
+    name, n, h, w, cin, cout, k, st, pad, ib, ob, il, ol, tile = case
     L = make_layer(name, h, w, cin, cout, k, st, pad, ib, ob)
     d = P.conv_desc(n, h, w, cin, cout, k, st, pad, ib, ob, il, ol)
-    assert P.ifq_conv_kernel_name(d).startswith("conv_win<"), P.ifq_conv_kernel_name(d)
+    assert P.ifq_conv_kernel_name(d) == "conv_win<%s>" % tile
     seed = zlib.crc32(name.encode()) % 983
     p = params_for(seed, L)
     x = codes_for(seed, (n, h, w, cin), ib)

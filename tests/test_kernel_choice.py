@@ -1,6 +1,9 @@
 """Which kernel the dispatcher takes where two or more cover a layer, on the CPU:
 layers measured with each of them (us in the comments, MI355X), on both sides of
 the line and a few percent or more apart."""
+import os
+import re
+
 import numpy as np
 import pytest
 
@@ -71,6 +74,37 @@ def test_kernels_with_an_identity_join():
     assert not join_name(8, 28, 28, 128, 128, 1, j).startswith("conv_win<")
     # windows too wide for the register-blocked kernels: 35.3, conv_win 43.7
     assert join_name(10, 80, 64, 448, 448, 2, j).startswith("conv_halo<")
+
+
+CSRC = os.path.join(os.path.dirname(P.__file__), "csrc")
+
+
+def test_every_windowed_instance_has_a_parity_case():
+    # a refit of the predictions must not leave a tile that still runs without a case:
+    # the parity cases name every tile of the table with each of the three inputs, and
+    # the dispatcher takes each case there
+    from test_gpu_win import CASES
+    with open(os.path.join(CSRC, "ifq_conv_win.hip")) as f:
+        tiles = re.findall(r"^    IFQ_WV\(([\d, ]+)\),", f.read(), re.M)
+    assert len(tiles) == 9
+    assert {c[13] for c in CASES} == {"%d, %s" % (i, t) for i in range(3) for t in tiles}
+    for n_, n, h, w, ci, co, k, st, pad, ib, ob, il, ol, tile in CASES:
+        d = P.conv_desc(n, h, w, ci, co, k, st, pad, ib, ob, il, ol)
+        assert P.ifq_conv_kernel_name(d) == "conv_win<%s>" % tile, n_
+
+
+def test_every_tile_of_the_tiled_and_the_general_kernel_has_a_parity_case():
+    from test_gpu_conv import TILED
+    from test_gpu_igemm import CASES
+    with open(os.path.join(CSRC, "ifq_conv_mfma.hip")) as f:
+        tiles = set(re.findall(r'"conv_mfma<([\d, ]+)>"', f.read()))
+    assert len(tiles) == 6 and {c[12] for c in TILED} == tiles
+    for n_, n, h, w, ci, co, k, st, pad, ob, il, ol, tile in TILED:
+        d = P.conv_desc(n, h, w, ci, co, k, st, pad, 2, ob, il, ol)
+        assert P.ifq_conv_kernel_name(d) == "conv_mfma<%s>" % tile, n_
+    with open(os.path.join(CSRC, "ifq_conv.hip")) as f:
+        names = set(re.findall(r'"(conv_igemm<[\d, ]+>)"', f.read()))
+    assert len(names) == 12 and {c[12] for c in CASES} == names
 
 
 @pytest.mark.parametrize("layer", [(16, 8, 64, 1024, 480), (10, 19, 64, 1152, 256),

@@ -71,3 +71,34 @@ def test_extension_is_built_for_this_interpreter(monkeypatch):
     monkeypatch.setattr(_ffi, "CALL_PATH", os.path.join(_ffi.HERE, "missing" + suffix))
     with pytest.raises(ImportError, match="missing.*is not built"):
         _ffi.load()
+
+
+class FakeCall:
+    """conv_forward that asks for a workspace of `need` bytes as the library does."""
+    def __init__(self, need):
+        self.need, self.seen = need, []
+
+    def conv_forward(self, d, x, w, thr, join, y, dump, ws, ws_bytes, stream):
+        self.seen.append((ws, ws_bytes, stream, dump))
+        return 0 if ws_bytes >= self.need else _ffi.IFQ_ERR_INSUFFICIENT_BUFFER
+
+
+def test_a_layer_that_needs_a_workspace_gets_one(monkeypatch):
+    from paper_1911_08076_amd import api
+    fake = FakeCall(4096)
+    monkeypatch.setattr(_ffi, "call", fake)
+    monkeypatch.setattr(api, "ifq_conv_workspace_bytes", lambda desc: 4096)
+    P.ifq_conv_forward(conv(1), X, X, THR, X, acc_dump=THR, stream=7)
+    (ws0, n0, s0, _), (ws1, n1, s1, dump) = fake.seen
+    assert ws0 is None and n0 == 0 and s0 == s1 == 7 and dump is THR
+    assert n1 == ws1.numel() == 4096 and ws1.device == X.device and not ws1.any()
+    # a workspace of the caller's that is too small is the caller's error, not retried
+    fake.seen.clear()
+    with pytest.raises(P.IfqError):
+        P.ifq_conv_forward(conv(1), X, X, THR, X, ws=torch.zeros(64, dtype=torch.uint8), stream=7)
+    assert len(fake.seen) == 1
+    # and one that is large enough is passed on
+    ws = torch.zeros(1024, dtype=torch.int32)
+    fake.seen.clear()
+    P.ifq_conv_forward(conv(1), X, X, THR, X, ws=ws, stream=7)
+    assert [(a is ws, b) for a, b, _, _ in fake.seen] == [(True, 4096)]

@@ -309,9 +309,9 @@ __global__ __launch_bounds__(64 * WM * WN * WK) void conv_mfma(ConvLaunch a) {
 // until the sums are added. Lane 16*q + r takes step q of a group for weight
 // row and image r, so one 16-byte load holds its codes for all four of the
 // group's MFMAs, the m-th of which contracts unit m of the four steps.
-// Measured: 6x6x256 -> 4096 at batch 32 on the 64 x 128 tiles above 43.3 us,
-// on 32 x 32 tiles through an LDS ring 15.3 us, here 8.4 us (4.5 TB/s of weights); 1x1x4096 ->
-// 4096 23.7, 9.8 and 5.1 us.
+// Measured at batch 32, calls in a row: 6x6x256 -> 4096 on the 64 x 128 tiles above
+// 43.0 us, here 9.5 us (4.0 TB/s of weights); 1x1x4096 -> 4096 23.6 and 5.9 us, -> 1000
+// sums 21.5 and 4.5 us.
 struct FcGeom {
   int32_t sn, sg, st;    // cells between images, channel blocks, taps
   FastDiv div_taps;
@@ -479,7 +479,7 @@ struct Variant {
   const char* name;
 };
 
-// Index order must match the switch in launch_conv_mfma. Fitted to 5349 layers, each
+// Index order must match the switch in launch_conv_mfma. Fitted to 5366 layers, each
 // timed on every tile (1x1 to 5x5, both layouts, every output and join): 2-bit codes
 // 5-8% rms (13% on the first tile), int32 sums 5-8%, the joins 5-15%, wider codes
 // 8-30%, which this kernel is never the fastest on.

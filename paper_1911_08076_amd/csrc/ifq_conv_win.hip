@@ -728,11 +728,11 @@ struct WinPlan {
 // cost 1.36, three 1.75 of one); per tile a fixed part and an epilogue by kind,
 // window loads, weight stages (barrier and latency, matrix cores) and K-group sums;
 // int32 sums the time of their bytes, which are the layer's largest stream. Fitted
-// to the variants that t_us picks, on 5349 layers in fragment order (1x1 to 5x5,
+// to the variants that t_us picks, on 5366 layers in fragment order (1x1 to 5x5,
 // every output and join; 5.1% rms) and 2000 byte and packed ones (7.2%).
-// t_us is 15 to 30% off on filters of one tap or a few, which one_clk was not
-// fitted to, but ranks the variants better than this does (1.8% behind the best
-// one on average against 2.3%).
+// t_us is 15 to 30% off on filters of one tap or a few, which it was not fitted to,
+// but ranks the variants a little better than this does (1.0% behind the best one on
+// average against 1.2%, 1.1 against 1.5 on byte codes).
 double win_estimate(const ConvLaunch& a, const WinVariant& V, const WinGeom& g, int64_t tiles,
                     int64_t lds, bool fr) {
   struct Kind {

@@ -6,8 +6,8 @@
 // widest that divides the bytes per pixel) and has every load of its window
 // in flight before the first compare; indexes are 32-bit with divisions by
 // multiplication. Before, each position's loads waited for the last compare
-// behind 64-bit divisions: 3x3/2 on 64x55x55x96 2-bit codes 6.7 -> 3.5 us,
-// on 32x13x13x256 5.7 -> 3.2 us, where a launch alone is 3.0 us.
+// behind 64-bit divisions: 3x3/2 on 64x55x55x96 2-bit codes 7.0 -> 3.9 us for calls in
+// a row (1.5 TB/s), on 32x13x13x256 6.9 -> 4.0, of which the kernel 5.9 -> 2.2.
 #include <hip/hip_runtime.h>
 
 #include "ifq_internal.h"
@@ -198,8 +198,8 @@ __device__ __forceinline__ v4u unpack16(uint32_t u) {
 }
 
 // Conversions by units of 16 channels. convert_codes moves four at a time,
-// one byte of a 2-bit layout per thread: 9.1 us for 64x56x56x64 bytes to
-// BLOCK64 (16 MB, 1.8 TB/s), here 3.3 us (4.9 TB/s; the launch alone is 3.0);
+// one byte of a 2-bit layout per thread: 9.4 us for 64x56x56x64 bytes to
+// BLOCK64 (16 MB, 1.7 TB/s), here 4.3 us (3.7 TB/s) for calls in a row;
 // 16x224x224x64 31 -> 10.5 us (6.1 TB/s). A thread has four units' loads in flight,
 // or one where four would leave CUs idle. Units run in
 // the order of the BLOCK64 side where there is one (unit 4*cell + j, so that

@@ -655,9 +655,8 @@ MfmaChoice choose_mfma(const ConvLaunch& a) {
 
 }  // namespace
 
-// The fast path picks the kernel with the lowest predicted time among the
-// register-blocked 3x3 kernels (one tile per workgroup or persistent), the
-// windowed 3x3 kernel and the tiled kernel. A fused downsample join runs on
+// The fast path picks the kernel with the lowest predicted time (plan_choice);
+// a fully connected layer runs on conv_fc. A fused downsample join runs on
 // the register-blocked kernel wherever it takes the layer (faster on every
 // downsampling block of the ResNet-18-shaped stack as measured), else on the
 // windowed kernel (the host checks fused_supported before launching one).

@@ -1,6 +1,7 @@
 // Integrated fixed-point quantized convolution on gfx950 (MI355X) for every
 // filter size and stride, from input windows resident in LDS: byte-per-code
-// input and 2-bit NHWC packed input with c_in a multiple of 16.
+// input and 2-bit NHWC packed input with c_in a multiple of 16, and 2-bit input of
+// either layout with c_in a multiple of 64.
 //
 // The integer part of Eq. (1), a = W_b (x) X_q, is an implicit GEMM
 // D[co][pixel] = sum_k W[co][k] * X[pixel][k] on v_mfma_i32_32x32x32_i8. What
@@ -941,7 +942,7 @@ bool win_eligible(const ConvLaunch& a, double* t_us) {
     if (a.in_bits == 8 || ((uintptr_t)a.x & 15)) return false;
   } else if (a.in_layout != IFQ_LAYOUT_U2_NHWC_PACKED || a.cin % 64 == 0 ||
              ((uintptr_t)a.x & 3)) {
-    return false;   // c_in % 64 == 0: the MFMA dispatcher's choice (plan_win)
+    return false;   // c_in % 64 == 0: the MFMA dispatcher's choice (plan_win_us)
   }
   WinPlan p;
   if (!choose_win(a, &p)) return false;

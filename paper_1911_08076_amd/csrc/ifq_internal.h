@@ -239,15 +239,11 @@ const char* conv_kernel_name(const ConvLaunch& a);
 // and the name of the variant it picks.
 bool mfma_eligible(const ConvLaunch& a);
 
-// 3x3 kernel with per-tile input windows in LDS (BLOCK64 input): the
-// variant, pixels per workgroup, workgroups along pixels and the predicted
-// time of the best variant that fits the layer, if any.
-// Predicted time (us) of a conv launch of `tiles` workgroup tiles of
-// tile_ops dense int8 ops each, occ of them sharing a CU: the launch, the
-// MFMA work of the busiest CU at a fitted efficiency eff, and a fitted fixed
-// cost c0_us per round of occ tiles on a CU (prologue latency, epilogue,
-// drain). One form for every kernel, so that the planners' predictions
-// compare.
+// Predicted time (us) of a launch of the windowed 3x3 kernel with `tiles`
+// workgroup tiles of tile_ops dense int8 ops each, occ of them sharing a CU: the
+// launch, the MFMA work of the busiest CU at a fitted efficiency eff, and a fitted
+// fixed cost c0_us per round of occ tiles on a CU (prologue latency, epilogue,
+// drain). The other kernels' fits stand beside their planners.
 constexpr double kLaunchUs = 2.0;
 constexpr int kPlanCUs = 256;
 constexpr double kCuOpsPerUsInt8 = 2.4e3 * 8192;   // dense int8 ops per us of one CU
@@ -262,6 +258,9 @@ inline double plan_time(int64_t tiles, double tile_ops, int occ, double c0_us, d
 // factor says how much of it its stores take beside its other work.
 constexpr double kSumBytesPerUs = 3.4e6;
 
+// 3x3 kernel with per-tile input windows in LDS (BLOCK64 input): the
+// variant, pixels per workgroup, workgroups along pixels and the predicted
+// time of the best variant that fits the layer, if any.
 struct HaloPlan {
   int variant;
   int bn;
@@ -391,7 +390,8 @@ inline bool fused_supported(const ConvLaunch& a) {
 }
 
 // Any filter size and stride on byte codes (below 8 bits) or 2-bit NHWC codes,
-// c_in a multiple of 16, input windows resident in LDS, and the predicted time.
+// c_in a multiple of 16 (2-bit codes with a multiple of 64: plan_win_us), input
+// windows resident in LDS, and the predicted time.
 bool win_eligible(const ConvLaunch& a, double* t_us);
 hipError_t launch_conv_win(const ConvLaunch& a, hipStream_t stream);
 const char* conv_win_name(const ConvLaunch& a);
